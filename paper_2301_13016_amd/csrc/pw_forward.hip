@@ -173,6 +173,15 @@ pw_status launch_forward(const FwdArgs &a, pw_dtype dt, const TileCfg &cfg, hipS
         c.wpb = 4;
         return launch_forward(a, dt, c, s);
     }
+    if (a.nx < cfg.px) {
+        // a row narrower than one lane's columns: the vectors of the last
+        // rows would run past the array (load_row needs rows of at least
+        // PX - 1 elements, load_epi of PX); one-column lanes give the same bits
+        TileCfg c = cfg;
+        c.px = 1;
+        c.share = 0;
+        return launch_forward(a, dt, c, s);
+    }
     if (cfg.share != 0) {
         switch (dt) {
             case PW_F32: return launch_forward_lds_f32(a, cfg, s);

@@ -77,6 +77,16 @@ template <typename T> __device__ __forceinline__ T right_of(T first, T halo, int
     return lane63 ? h : s;
 }
 
+// A value in storage precision from one lane (as lane_value, any type).
+template <typename T> __device__ __forceinline__ T stored_lane_value(T x, int lane) {
+    if constexpr (sizeof(T) == 2) {
+        const uint32_t b = __builtin_bit_cast(uint16_t, x);
+        return __builtin_bit_cast(T, static_cast<uint16_t>(__builtin_amdgcn_readlane(static_cast<int>(b), lane)));
+    } else {
+        return lane_value(x, lane);
+    }
+}
+
 // Read of a kernel-invariant array at a wave-uniform index through the
 // constant address space, so that it becomes a scalar load (counted apart from
 // the vector loads in flight: waiting for it does not drain the prefetch).
@@ -221,6 +231,12 @@ template <int RY> struct StripAddr {
     uint32_t yany;           // OR of ycode (wave-uniform)
     uint32_t hcode;
     uint32_t xhalo;
+    // strips at the x end (not Full, PX > 1): the largest offset at which a
+    // vector still ends inside the array's last plane (wave-uniform, see
+    // load_row), and a bit per element m of the lane's columns that is the
+    // first right-halo column (boundary rules, see bc_patch_x)
+    uint32_t lim;
+    uint32_t xpatch;
 };
 
 // The value rules of one freshly loaded plane, applied in place before its
@@ -288,36 +304,58 @@ __device__ __forceinline__ void bc_strip_codes(StripAddr<RY> &s, uint32_t bcv, i
     }
 }
 
-// PX consecutive elements of one row starting at padded column `col`.  In a
-// full strip (Full) every lane's vector lies inside the row and is read with
-// one vector load; in the strip at the x end of the grid every lane reads
-// element-wise with the columns clamped into the row (every column a stored
-// output reads is in range, so clamping only affects values that are not
-// used) and, in kernels built for boundary rules (Bc), then mapped by the
-// axis' rule (bc_src over n interior columns, halo h).  One-column lanes need
-// no clamping beyond their start column unless mapped.  The choice is made
-// per wavefront, so neither path branches per lane.
+// PX consecutive elements of one row starting at padded column `col` (byte
+// offset `off` in the plane).  One vector load per lane in every strip.  In
+// the strip at the x end of the grid the vectors of the last lanes run past
+// the row's end into the next row (lanes wholly past the end start at the
+// last column, so by at most PX-1 elements): values that no stored output
+// reads, since a lane's stored columns end at the row's interior and take
+// their right neighbour from the row's halo, still inside the row.  Only the
+// last row of the array's last plane has no memory behind it; there `lim`
+// (every other plane: no limit) pulls the start back, which moves other
+// columns into the last lanes of that row -- the halo edge row above the top
+// plane, which no output reads (with rows of at least PX - 1 elements, which
+// the launch sees to).  These strips once loaded every element by itself from a
+// clamped address, four times the load instructions of a full strip and as
+// many cache requests per byte: 201x143x117 FP32 took 47.4 us, now 29.7 in the
+// same launch shape.  Kernels built for boundary rules (Bc) read one-column lanes
+// at the mapped column and patch wider ones afterwards (bc_patch_x).
 template <typename Tin, int PX, bool Full, int Bc = 0>
-__device__ __forceinline__ void load_row(typename Vec<Tin, PX>::type &dst, const char *plane, uint32_t off, int col,
-                                         int last_col, int n, int h, int bc) {
-    if constexpr (Full || (PX == 1 && !Bc)) {
-        (void)col;
-        (void)last_col;
-        (void)n;
-        (void)h;
-        (void)bc;
-        using VT = typename Vec<Tin, PX>::type;
+__device__ __forceinline__ void load_row(typename Vec<Tin, PX>::type &dst, const char *plane, uint32_t off,
+                                         uint32_t lim, int col, int last_col, int n, int h, int bc) {
+    using VT = typename Vec<Tin, PX>::type;
+    if constexpr (PX == 1 && Bc) {
+        const char *row = plane + off - static_cast<int64_t>(col) * static_cast<int64_t>(sizeof(Tin));
+        dst = PW_GLOAD(Tin, row + static_cast<int64_t>(bc_map<Bc>(min(col, last_col), n, h, bc)) *
+                                      static_cast<int64_t>(sizeof(Tin)));
+    } else if constexpr (Full || PX == 1) {
         dst = PW_GLOAD(VT, plane + off);
     } else {
-        const char *row = plane + off - static_cast<int64_t>(col) * static_cast<int64_t>(sizeof(Tin));
+        dst = PW_GLOAD(VT, plane + min(off, lim));
+    }
+}
+
+// The limit load_row takes for padded plane kp: only the array's last plane
+// has one (wave-uniform).
+__device__ __forceinline__ uint32_t plane_lim(int kp, int last_plane, uint32_t lim) {
+    return kp == last_plane ? lim : 0xffffffffu;
+}
+
+// Boundary rules on x (Bc), lanes of several columns, strips at the x end:
+// the element that is the first right-halo column takes its mapped value,
+// which the packed halo load fetched (lane 32+r: row r).
+template <typename Tin, int PX, int RY>
+__device__ __forceinline__ void bc_patch_x(Plane<Tin, PX, RY> &P, const StripAddr<RY> &s) {
+#pragma unroll
+    for (int r = 0; r < RY + 2; ++r) {
+        const Tin xu = stored_lane_value(P.hu, 32 + r), xv = stored_lane_value(P.hv, 32 + r),
+                  xw = stored_lane_value(P.hw, 32 + r);
 #pragma unroll
         for (int m = 0; m < PX; ++m) {
-            const Tin x = PW_GLOAD(Tin, row + static_cast<int64_t>(bc_map<Bc>(min(col + m, last_col), n, h, bc)) *
-                                               static_cast<int64_t>(sizeof(Tin)));
-            if constexpr (PX == 1)
-                dst = x;
-            else
-                dst[m] = x;
+            const bool at = (s.xpatch >> m) & 1u;
+            P.u[r][m] = at ? xu : static_cast<Tin>(P.u[r][m]);
+            P.v[r][m] = at ? xv : static_cast<Tin>(P.v[r][m]);
+            P.w[r][m] = at ? xw : static_cast<Tin>(P.w[r][m]);
         }
     }
 }
@@ -329,11 +367,12 @@ __device__ __forceinline__ void load_plane(Plane<Tin, PX, RY> &P, const FwdK<Tin
     const char *bu = reinterpret_cast<const char *>(a.u) + pb;
     const char *bv = reinterpret_cast<const char *>(a.v) + pb;
     const char *bw = reinterpret_cast<const char *>(a.w) + pb;
+    const uint32_t lim = plane_lim(kp, a.nz + 2 * a.h - 1, s.lim);
 #pragma unroll
     for (int r = 0; r < RY + 2; ++r) {
-        load_row<Tin, PX, Full, Bc>(P.u[r], bu, s.roff[r], s.col, last_col, a.nx, a.h, a.bcx);
-        load_row<Tin, PX, Full, Bc>(P.v[r], bv, s.roff[r], s.col, last_col, a.nx, a.h, a.bcx);
-        load_row<Tin, PX, Full, Bc>(P.w[r], bw, s.roff[r], s.col, last_col, a.nx, a.h, a.bcx);
+        load_row<Tin, PX, Full, Bc>(P.u[r], bu, s.roff[r], lim, s.col, last_col, a.nx, a.h, a.bcx);
+        load_row<Tin, PX, Full, Bc>(P.v[r], bv, s.roff[r], lim, s.col, last_col, a.nx, a.h, a.bcx);
+        load_row<Tin, PX, Full, Bc>(P.w[r], bw, s.roff[r], lim, s.col, last_col, a.nx, a.h, a.bcx);
     }
     P.hu = PW_GLOAD(Tin, bu + s.hoff);
     P.hv = PW_GLOAD(Tin, bv + s.hoff);
@@ -352,40 +391,81 @@ template <typename T, int N> __device__ __forceinline__ void store_vec(char *p, 
     PW_GSTORE_NT(VT, v, p);
 }
 
+// Stores of the strip at the x end: lanes whose N columns all lie in the grid
+// store one vector, the one lane that straddles the end its first columns.
+// Vectors of 16 bytes go out non-temporally as in full strips, narrower ones
+// write-back: a wavefront's piece of a row then has more line ends for its
+// length, whose parts L2 merges with the next piece's.  Measured (FP32, new /
+// old kind of store): four columns per lane 23.2 / 24.6 us at 201x143x117,
+// 46.8 / 48.4 at 300x300x75, 100.3 / 103.8 at 1000x300x64; one column per lane
+// write-back 49.0, non-temporal 52.8 us at 300x300x75, 72.1 / 78.1 at 60x1000x200.
+template <typename T, int N>
+__device__ __forceinline__ void store_edge(char *p, const T (&x)[N], int nvalid) {
+    if (nvalid >= N) {
+        typename Vec<T, N>::type v;
+        if constexpr (N == 1) {
+            v = x[0];
+        } else {
+#pragma unroll
+            for (int m = 0; m < N; ++m) v[m] = x[m];
+        }
+        using VT = typename Vec<T, N>::type;
+        if constexpr (N * sizeof(T) >= 16)
+            PW_GSTORE_NT(VT, v, p);
+        else
+            PW_GSTORE(VT, v, p);
+    } else if constexpr (N > 1) {
+#pragma unroll
+        for (int m = 0; m < N - 1; ++m)
+            if (m < nvalid) PW_GSTORE(T, x[m], p + m * sizeof(T));
+    }
+}
+
 // The epilogue's addend rows of one output level (output layout, compute
-// type): RY rows x PX columns, columns clamped into the grid (the columns
-// past the end are never stored).
+// type): RY rows x PX columns, one vector per row.  In the strip at the x end
+// a lane whose vector would run past the row starts at column nx - PX instead
+// (the launch gives such strips only to grids with nx >= PX); epi_shift moves
+// the straddling lane's columns back into place at their first use.
 template <typename Tin, int PX, int RY> struct EpiRows {
     using Tc = typename Storage<Tin>::Tc;
     typename Vec<Tc, PX>::type u[RY], v[RY], w[RY];
 };
 
-template <typename Tin, int PX, int RY, bool Full>
+template <typename Tin, int PX, int RY>
 __device__ __forceinline__ void load_epi(EpiRows<Tin, PX, RY> &E, const FwdK<Tin> &a, int kk,
-                                         const uint32_t (&ooff)[RY], int ic) {
+                                         const uint32_t (&eoff)[RY]) {
     using Tc = typename Storage<Tin>::Tc;
+    using VT = typename Vec<Tc, PX>::type;
     const int64_t ob = static_cast<int64_t>(kk) * a.out_sz * static_cast<int64_t>(sizeof(Tc));
     const char *bu = reinterpret_cast<const char *>(a.cu) + ob;
     const char *bv = reinterpret_cast<const char *>(a.cv) + ob;
     const char *bw = reinterpret_cast<const char *>(a.cw) + ob;
 #pragma unroll
     for (int r = 0; r < RY; ++r) {
-        if constexpr (Full || PX == 1) {
-            using VT = typename Vec<Tc, PX>::type;
-            E.u[r] = PW_GLOAD_NT(VT, bu + ooff[r]);
-            E.v[r] = PW_GLOAD_NT(VT, bv + ooff[r]);
-            E.w[r] = PW_GLOAD_NT(VT, bw + ooff[r]);
-        } else {
-            // ooff is at column ic = min(ii0, nx-1); columns ic+m clamped to nx-1
+        E.u[r] = PW_GLOAD_NT(VT, bu + eoff[r]);
+        E.v[r] = PW_GLOAD_NT(VT, bv + eoff[r]);
+        E.w[r] = PW_GLOAD_NT(VT, bw + eoff[r]);
+    }
+}
+
+// Elements d.. of a vector moved down to element 0 (d in 0..N-1, per lane;
+// the elements past N-1-d are left undefined).
+template <typename T, int N>
+__device__ __forceinline__ void epi_shift(typename Vec<T, N>::type &v, uint32_t d) {
+    if constexpr (N > 1) {
 #pragma unroll
-            for (int m = 0; m < PX; ++m) {
-                const int64_t d = static_cast<int64_t>(min(ic + m, a.nx - 1) - ic) * sizeof(Tc);
-                E.u[r][m] = PW_GLOAD_NT(Tc, bu + ooff[r] + d);
-                E.v[r][m] = PW_GLOAD_NT(Tc, bv + ooff[r] + d);
-                E.w[r][m] = PW_GLOAD_NT(Tc, bw + ooff[r] + d);
-            }
+        for (int b = N / 2; b >= 1; b /= 2) {
+            const bool on = d & static_cast<uint32_t>(b);
+#pragma unroll
+            for (int m = 0; m + b < N; ++m) v[m] = on ? v[m + b] : v[m];
         }
     }
+}
+// First output column whose addend vector lane starting at column i0 loads,
+// on rows of n columns (n >= N), and how far its columns are shifted.
+template <int N> __device__ __forceinline__ int epi_col(int i0, int n) { return N == 1 ? min(i0, n - 1) : min(i0, n - N); }
+template <int N> __device__ __forceinline__ uint32_t epi_off(int i0, int n) {
+    return N == 1 ? 0u : static_cast<uint32_t>(min(i0 - epi_col<N>(i0, n), N - 1));
 }
 
 // Source terms of output level kk (interior numbering) from planes kk-1 (m),
@@ -395,7 +475,7 @@ __device__ __forceinline__ void level(const Plane<Tin, PX, RY> &m, const Plane<T
                                       const Plane<Tin, PX, RY> &p,
                                       const FwdK<Tin> &a, int kk, bool lane0, bool lane63, int nvalid,
                                       const uint32_t (&ooff)[RY], const bool (&row_ok)[RY],
-                                      const EpiRows<Tin, PX, RY> &E) {
+                                      EpiRows<Tin, PX, RY> &E, uint32_t eshift) {
     using Tc = typename Storage<Tin>::Tc;
     // element (row r, column x) of a loaded row array, widened
 #define G(arr, r, x) Storage<Tin>::widen(comp<Tin, PX>((arr)[r], (x)))
@@ -444,6 +524,11 @@ __device__ __forceinline__ void level(const Plane<Tin, PX, RY> &m, const Plane<T
     for (int r = 0; r < RY; ++r) {
         const int q = r + 1;   // this output row within the loaded rows
         Tc rsu[PX], rsv[PX], rsw[PX];
+        if constexpr (Epi && !Full) {
+            epi_shift<Tc, PX>(E.u[r], eshift);
+            epi_shift<Tc, PX>(E.v[r], eshift);
+            epi_shift<Tc, PX>(E.w[r], eshift);
+        }
 #pragma unroll
         for (int x = 0; x < PX; ++x) {
             // su: x faces (u+u), y faces (v+v at i, i+1), z faces (w+w at i, i+1)
@@ -501,14 +586,9 @@ __device__ __forceinline__ void level(const Plane<Tin, PX, RY> &m, const Plane<T
                 store_vec<Tc, PX>(osv + ooff[r], rsv);
                 store_vec<Tc, PX>(osw + ooff[r], rsw);
             } else {
-#pragma unroll
-                for (int x = 0; x < PX; ++x) {
-                    if (x < nvalid) {
-                        PW_GSTORE(Tc, rsu[x], osu + ooff[r] + x * sizeof(Tc));
-                        PW_GSTORE(Tc, rsv[x], osv + ooff[r] + x * sizeof(Tc));
-                        PW_GSTORE(Tc, rsw[x], osw + ooff[r] + x * sizeof(Tc));
-                    }
-                }
+                store_edge<Tc, PX>(osu + ooff[r], rsu, nvalid);
+                store_edge<Tc, PX>(osv + ooff[r], rsv, nvalid);
+                store_edge<Tc, PX>(osw + ooff[r], rsw, nvalid);
             }
         }
     }
@@ -559,13 +639,19 @@ __device__ __forceinline__ void strip_march_t(const FwdK<Tin> &a, int tx, int ty
     {   // packed halo: lane r -> left halo of row r, lane 32+r -> right halo of row r
         const int hr = min(lane & 31, RY + 1);
         const int hrow_p = min(jj0 - 1 + a.h + hr, prows - 1);
-        const int hcol_p = (lane & 32) ? min(tx * 64 * PX + 64 * PX + a.h, last_col) : tx * 64 * PX + a.h - 1;
+        // (wide-lane strips at the x end under boundary rules: the first right-halo
+        // column instead, for bc_patch_x; there no lane 63 output reads the
+        // column right of the strip)
+        const int hright = (Bc && !Full && PX > 1) ? a.nx + a.h : min(tx * 64 * PX + 64 * PX + a.h, last_col);
+        const int hcol_p = (lane & 32) ? hright : tx * 64 * PX + a.h - 1;
         const int hrow = bc_map<Bc>(hrow_p, a.ny, a.h, a.bcy);
         const int hcol = bc_map<Bc>(hcol_p, a.nx, a.h, a.bcx);
         s.hoff = static_cast<uint32_t>((hrow * a.in_sy + hcol) * static_cast<int>(sizeof(Tin)));
         bc_strip_codes<Bc, PX, RY>(s, a.bcv, jj0, prows, last_col, hrow_p, hcol_p, a.nx, a.ny, a.h);
     }
-    uint32_t ooff[RY];
+    s.lim = static_cast<uint32_t>(((prows - 1) * a.in_sy + pcols - PX) * static_cast<int>(sizeof(Tin)));
+    s.xpatch = (a.nx - ii0 >= 0 && a.nx - ii0 < PX) ? 1u << (a.nx - ii0) : 0u;
+    uint32_t ooff[RY], eoff[RY];
     bool row_ok[RY];
 #pragma unroll
     for (int r = 0; r < RY; ++r) {
@@ -573,9 +659,10 @@ __device__ __forceinline__ void strip_march_t(const FwdK<Tin> &a, int tx, int ty
         const int jj = min(jj0 + r, a.ny - 1);
         const int ic = min(ii0, a.nx - 1);
         ooff[r] = static_cast<uint32_t>((jj * a.out_sy + ic) * static_cast<int>(sizeof(Tc)));
+        eoff[r] = static_cast<uint32_t>((jj * a.out_sy + epi_col<PX>(ii0, a.nx)) * static_cast<int>(sizeof(Tc)));
     }
     const bool lane0 = lane == 0, lane63 = lane == 63;
-    const int ic = min(ii0, a.nx - 1);
+    const uint32_t eshift = epi_off<PX>(ii0, a.nx);
 
     const int k0 = cz * a.zlen;
     const int k1 = min(a.nz, k0 + a.zlen);
@@ -588,6 +675,11 @@ __device__ __forceinline__ void strip_march_t(const FwdK<Tin> &a, int tx, int ty
     // merge drains every outstanding load, prefetch included.
     // (value rules: a plane's z codes are set with its load, and the rules are
     // applied to it just before the first level that reads it)
+#define PW_RULES(P)                                                                \
+    do {                                                                           \
+        if constexpr (Bc && !Full && PX > 1) bc_patch_x<Tin, PX, RY>(P, s);        \
+        if constexpr (Bc == 2) bc_values<Tin, PX, RY, Full>(P, s, a.bcv);          \
+    } while (0)
 #define PW_PLOAD(P, kp)                                                                                        \
     do {                                                                                                       \
         load_plane<Tin, PX, RY, Full, Bc>(P, a, bc_map<Bc>(min((kp), k1) + h, a.nz, h, a.bcz), s, last_col); \
@@ -596,15 +688,15 @@ __device__ __forceinline__ void strip_march_t(const FwdK<Tin> &a, int tx, int ty
 #define PW_LOAD(P, kp)                                                   \
     do {                                                                 \
         if constexpr (Epi) {                                             \
-            load_epi<Tin, PX, RY, Full>(Ep, a, kk, ooff, ic);            \
+            load_epi<Tin, PX, RY>(Ep, a, kk, eoff);                      \
             __builtin_amdgcn_sched_barrier(0);                           \
         }                                                                \
         PW_PLOAD(P, kp);                                                 \
     } while (0)
 #define PW_LEVEL(M, C, P)                                                                      \
     do {                                                                                       \
-        if constexpr (Bc == 2) bc_values<Tin, PX, RY, Full>(P, s, a.bcv);                      \
-        level<Tin, PX, RY, Full, Epi>(M, C, P, a, kk, lane0, lane63, nvalid, ooff, row_ok, Ep); \
+        PW_RULES(P);                                                                           \
+        level<Tin, PX, RY, Full, Epi>(M, C, P, a, kk, lane0, lane63, nvalid, ooff, row_ok, Ep, eshift); \
     } while (0)
 #define PW_FIRST(P, kp)                                                                            \
     do {                                                                                           \
@@ -613,10 +705,8 @@ __device__ __forceinline__ void strip_march_t(const FwdK<Tin> &a, int tx, int ty
     } while (0)
 #define PW_FIX_FIRST(A, B)                                   \
     do {                                                     \
-        if constexpr (Bc == 2) {                             \
-            bc_values<Tin, PX, RY, Full>(A, s, a.bcv);       \
-            bc_values<Tin, PX, RY, Full>(B, s, a.bcv);       \
-        }                                                    \
+        PW_RULES(A);                                         \
+        PW_RULES(B);                                         \
     } while (0)
     int kk = k0;
     if constexpr (Depth == 1) {
@@ -667,6 +757,7 @@ __device__ __forceinline__ void strip_march_t(const FwdK<Tin> &a, int tx, int ty
             if (++kk >= k1) break;
         }
     }
+#undef PW_RULES
 #undef PW_PLOAD
 #undef PW_LOAD
 #undef PW_FIRST
@@ -762,6 +853,7 @@ __device__ __forceinline__ void load_plane_own(Plane<Tin, PX, RY> &P, const FwdK
     const char *bw = reinterpret_cast<const char *>(a.w) + pb;
     constexpr int r0 = (Role == kRoleLo) ? 0 : 1;
     constexpr int r1 = (Role == kRoleHi) ? RY + 1 : RY;
+    const uint32_t lim = plane_lim(kp, a.nz + 2 * a.h - 1, s.lim);
 #pragma unroll
     for (int r = r0; r <= r1; ++r) {
         const bool shared = r == 0 || r == RY + 1 || (Role == kRoleLo && r == 1) || (Role == kRoleHi && r == RY);
@@ -772,9 +864,9 @@ __device__ __forceinline__ void load_plane_own(Plane<Tin, PX, RY> &P, const FwdK
             P.w[r] = PW_GLOAD_NT(VT, bw + s.roff[r]);
             continue;
         }
-        load_row<Tin, PX, Full, Bc>(P.u[r], bu, s.roff[r], s.col, last_col, a.nx, a.h, a.bcx);
-        load_row<Tin, PX, Full, Bc>(P.v[r], bv, s.roff[r], s.col, last_col, a.nx, a.h, a.bcx);
-        load_row<Tin, PX, Full, Bc>(P.w[r], bw, s.roff[r], s.col, last_col, a.nx, a.h, a.bcx);
+        load_row<Tin, PX, Full, Bc>(P.u[r], bu, s.roff[r], lim, s.col, last_col, a.nx, a.h, a.bcx);
+        load_row<Tin, PX, Full, Bc>(P.v[r], bv, s.roff[r], lim, s.col, last_col, a.nx, a.h, a.bcx);
+        load_row<Tin, PX, Full, Bc>(P.w[r], bw, s.roff[r], lim, s.col, last_col, a.nx, a.h, a.bcx);
     }
     P.hu = PW_GLOAD(Tin, bu + s.hoff);
     P.hv = PW_GLOAD(Tin, bv + s.hoff);
@@ -843,13 +935,19 @@ __device__ __forceinline__ void strip_march_lds_t(const FwdK<Tin> &a, EdgeLds<Ti
     {
         const int hr = min(lane & 31, RY + 1);
         const int hrow_p = min(jj0 - 1 + a.h + hr, prows - 1);
-        const int hcol_p = (lane & 32) ? min(tx * 64 * PX + 64 * PX + a.h, last_col) : tx * 64 * PX + a.h - 1;
+        // (wide-lane strips at the x end under boundary rules: the first right-halo
+        // column instead, for bc_patch_x; there no lane 63 output reads the
+        // column right of the strip)
+        const int hright = (Bc && !Full && PX > 1) ? a.nx + a.h : min(tx * 64 * PX + 64 * PX + a.h, last_col);
+        const int hcol_p = (lane & 32) ? hright : tx * 64 * PX + a.h - 1;
         const int hrow = bc_map<Bc>(hrow_p, a.ny, a.h, a.bcy);
         const int hcol = bc_map<Bc>(hcol_p, a.nx, a.h, a.bcx);
         s.hoff = static_cast<uint32_t>((hrow * a.in_sy + hcol) * static_cast<int>(sizeof(Tin)));
         bc_strip_codes<Bc, PX, RY>(s, a.bcv, jj0, prows, last_col, hrow_p, hcol_p, a.nx, a.ny, a.h);
     }
-    uint32_t ooff[RY];
+    s.lim = static_cast<uint32_t>(((prows - 1) * a.in_sy + pcols - PX) * static_cast<int>(sizeof(Tin)));
+    s.xpatch = (a.nx - ii0 >= 0 && a.nx - ii0 < PX) ? 1u << (a.nx - ii0) : 0u;
+    uint32_t ooff[RY], eoff[RY];
     bool row_ok[RY];
 #pragma unroll
     for (int r = 0; r < RY; ++r) {
@@ -857,9 +955,10 @@ __device__ __forceinline__ void strip_march_lds_t(const FwdK<Tin> &a, EdgeLds<Ti
         const int jj = min(jj0 + r, a.ny - 1);
         const int ic = min(ii0, a.nx - 1);
         ooff[r] = static_cast<uint32_t>((jj * a.out_sy + ic) * static_cast<int>(sizeof(Tc)));
+        eoff[r] = static_cast<uint32_t>((jj * a.out_sy + epi_col<PX>(ii0, a.nx)) * static_cast<int>(sizeof(Tc)));
     }
     const bool lane0 = lane == 0, lane63 = lane == 63;
-    const int ic = min(ii0, a.nx - 1);
+    const uint32_t eshift = epi_off<PX>(ii0, a.nx);
 
     const int k0 = cz * a.zlen;
     const int k1 = min(a.nz, k0 + a.zlen);
@@ -878,7 +977,7 @@ __device__ __forceinline__ void strip_march_lds_t(const FwdK<Tin> &a, EdgeLds<Ti
 #define PW_LOAD(P, kp)                                                   \
     do {                                                                 \
         if constexpr (Epi) {                                             \
-            load_epi<Tin, PX, RY, Full>(Ep, a, kk, ooff, ic);            \
+            load_epi<Tin, PX, RY>(Ep, a, kk, eoff);                      \
             __builtin_amdgcn_sched_barrier(0);                           \
         }                                                                \
         PW_PLOAD(P, kp);                                                 \
@@ -889,12 +988,13 @@ __device__ __forceinline__ void strip_march_lds_t(const FwdK<Tin> &a, EdgeLds<Ti
         __syncthreads();                                                 \
         get_edges<Tin, PX, RY, W, Role>(L, slot, wave, lane, P);         \
         slot = slot == kLdsSlots - 1 ? 0 : slot + 1;                     \
+        if constexpr (Bc && !Full && PX > 1) bc_patch_x<Tin, PX, RY>(P, s); \
         if constexpr (Bc == 2) bc_values<Tin, PX, RY, Full>(P, s, a.bcv); \
     } while (0)
 #define PW_LEVEL(M, C, P)                                                                          \
     do {                                                                                           \
         PW_SHARE(P);                                                                               \
-        level<Tin, PX, RY, Full, Epi>(M, C, P, a, kk, lane0, lane63, nvalid, ooff, row_ok, Ep);   \
+        level<Tin, PX, RY, Full, Epi>(M, C, P, a, kk, lane0, lane63, nvalid, ooff, row_ok, Ep, eshift); \
     } while (0)
     int kk = k0;
     if constexpr (Depth == 1) {

@@ -148,14 +148,9 @@ __device__ __forceinline__ void level_tl(const Plane<T, PX, RY> &xm, const Plane
                 store_vec<T, PX>(otv + ooff[r], rtv);
                 store_vec<T, PX>(otw + ooff[r], rtw);
             } else {
-#pragma unroll
-                for (int x = 0; x < PX; ++x) {
-                    if (x < nvalid) {
-                        reinterpret_cast<T *>(otu + ooff[r])[x] = rtu[x];
-                        reinterpret_cast<T *>(otv + ooff[r])[x] = rtv[x];
-                        reinterpret_cast<T *>(otw + ooff[r])[x] = rtw[x];
-                    }
-                }
+                store_edge<T, PX>(otu + ooff[r], rtu, nvalid);
+                store_edge<T, PX>(otv + ooff[r], rtv, nvalid);
+                store_edge<T, PX>(otw + ooff[r], rtw, nvalid);
             }
         }
     }
@@ -190,6 +185,7 @@ __device__ __forceinline__ void tl_march(const FwdK<T> &a, const FwdK<T> &d, int
         const int hcol = (lane & 32) ? min(tx * 64 * PX + 64 * PX + a.h, last_col) : tx * 64 * PX + a.h - 1;
         s.hoff = static_cast<uint32_t>((hrow * a.in_sy + hcol) * static_cast<int>(sizeof(T)));
     }
+    s.lim = static_cast<uint32_t>(((prows - 1) * a.in_sy + pcols - PX) * static_cast<int>(sizeof(T)));
     uint32_t ooff[RY];
     bool row_ok[RY];
 #pragma unroll

@@ -32,6 +32,13 @@ TileCfg default_zfast_tile(const FwdArgs &a, pw_dtype dt) {
 
 pw_status launch_zfast(const FwdArgs &a, pw_dtype dt, const TileCfg &cfg, hipStream_t s) {
     if (!zfast_tile_supported(cfg, dt)) return fail(PW_ERR_INVALID_ARG, "unsupported z-fastest tile configuration");
+    if (a.epilogue && a.nz < cfg.px) {
+        // columns shorter than one lane's levels: one-level lanes (the same
+        // bits), see load_zepi
+        TileCfg c = cfg;
+        c.px = 1;
+        return launch_zfast(a, dt, c, s);
+    }
     switch (dt) {
         case PW_F32: return launch_zfast_f32(a, cfg, s);
         case PW_F64: return launch_zfast_f64(a, cfg, s);

@@ -64,6 +64,7 @@ template <int RJ> struct ZAddr {
     uint32_t roff[RJ + 2];   // byte offset, within an x-plane, of this lane's first level in row r
     uint32_t hoff;           // byte offset of this lane's halo element
     int kcol;                // padded level of the lane's first element
+    uint32_t lim;            // largest offset of a vector in the array's last x-plane (see load_row)
 };
 
 template <typename Tin, int PZ, int RJ, bool Full>
@@ -73,11 +74,12 @@ __device__ __forceinline__ void load_xplane(ZPlane<Tin, PZ, RJ> &P, const ZfK<Ti
     const char *bu = reinterpret_cast<const char *>(a.u) + pb;
     const char *bv = reinterpret_cast<const char *>(a.v) + pb;
     const char *bw = reinterpret_cast<const char *>(a.w) + pb;
+    const uint32_t lim = plane_lim(ip, a.nx + 2 * a.h - 1, s.lim);
 #pragma unroll
     for (int r = 0; r < RJ + 2; ++r) {
-        load_row<Tin, PZ, Full>(P.u[r], bu, s.roff[r], s.kcol, last_k, a.nz, a.h, PW_HALO_KEEP);
-        load_row<Tin, PZ, Full>(P.v[r], bv, s.roff[r], s.kcol, last_k, a.nz, a.h, PW_HALO_KEEP);
-        load_row<Tin, PZ, Full>(P.w[r], bw, s.roff[r], s.kcol, last_k, a.nz, a.h, PW_HALO_KEEP);
+        load_row<Tin, PZ, Full>(P.u[r], bu, s.roff[r], lim, s.kcol, last_k, a.nz, a.h, PW_HALO_KEEP);
+        load_row<Tin, PZ, Full>(P.v[r], bv, s.roff[r], lim, s.kcol, last_k, a.nz, a.h, PW_HALO_KEEP);
+        load_row<Tin, PZ, Full>(P.w[r], bw, s.roff[r], lim, s.kcol, last_k, a.nz, a.h, PW_HALO_KEEP);
     }
     P.hu = PW_GLOAD(Tin, bu + s.hoff);
     P.hv = PW_GLOAD(Tin, bv + s.hoff);
@@ -88,37 +90,26 @@ template <typename Tc, int PZ> struct LaneCoeffs {
     Tc z1[PZ], z2[PZ], d1[PZ], d2[PZ];
 };
 
-// The epilogue's addends of one output column: RJ rows x PZ levels, levels
-// clamped into the column (those past the end are never stored).
+// The epilogue's addends of one output column: RJ rows x PZ levels, one vector
+// per row, shifted into the column at its end (see EpiRows).
 template <typename Tc, int PZ, int RJ> struct ZEpi {
     typename Vec<Tc, PZ>::type u[RJ], v[RJ], w[RJ];
 };
 
-template <typename Tin, int PZ, int RJ, bool Full>
+template <typename Tin, int PZ, int RJ>
 __device__ __forceinline__ void load_zepi(ZEpi<typename Storage<Tin>::Tc, PZ, RJ> &E, const ZfK<Tin> &a, int ii,
-                                          const uint32_t (&ooff)[RJ], int kc) {
+                                          const uint32_t (&eoff)[RJ]) {
     using Tc = typename Storage<Tin>::Tc;
+    using VT = typename Vec<Tc, PZ>::type;
     const int64_t ob = static_cast<int64_t>(ii) * a.out_si * static_cast<int64_t>(sizeof(Tc));
     const char *bu = reinterpret_cast<const char *>(a.cu) + ob;
     const char *bv = reinterpret_cast<const char *>(a.cv) + ob;
     const char *bw = reinterpret_cast<const char *>(a.cw) + ob;
 #pragma unroll
     for (int r = 0; r < RJ; ++r) {
-        if constexpr (Full || PZ == 1) {
-            using VT = typename Vec<Tc, PZ>::type;
-            E.u[r] = PW_GLOAD_NT(VT, bu + ooff[r]);
-            E.v[r] = PW_GLOAD_NT(VT, bv + ooff[r]);
-            E.w[r] = PW_GLOAD_NT(VT, bw + ooff[r]);
-        } else {
-            // ooff is at level kc = min(kk0, nz-1); levels kc+m clamped to nz-1
-#pragma unroll
-            for (int m = 0; m < PZ; ++m) {
-                const int64_t d = static_cast<int64_t>(min(kc + m, a.nz - 1) - kc) * sizeof(Tc);
-                E.u[r][m] = PW_GLOAD_NT(Tc, bu + ooff[r] + d);
-                E.v[r][m] = PW_GLOAD_NT(Tc, bv + ooff[r] + d);
-                E.w[r][m] = PW_GLOAD_NT(Tc, bw + ooff[r] + d);
-            }
-        }
+        E.u[r] = PW_GLOAD_NT(VT, bu + eoff[r]);
+        E.v[r] = PW_GLOAD_NT(VT, bv + eoff[r]);
+        E.w[r] = PW_GLOAD_NT(VT, bw + eoff[r]);
     }
 }
 
@@ -131,7 +122,7 @@ __device__ __forceinline__ void column(const ZPlane<Tin, PZ, RJ> &m, const ZPlan
                                        const ZPlane<Tin, PZ, RJ> &p, const ZfK<Tin> &a, int ii, bool lane0,
                                        bool lane63, int nvalid, const uint32_t (&ooff)[RJ], const bool (&row_ok)[RJ],
                                        const LaneCoeffs<typename Storage<Tin>::Tc, PZ> &K,
-                                       const ZEpi<typename Storage<Tin>::Tc, PZ, RJ> &E) {
+                                       ZEpi<typename Storage<Tin>::Tc, PZ, RJ> &E, uint32_t eshift) {
     using Tc = typename Storage<Tin>::Tc;
 #define G(arr, r, x) Storage<Tin>::widen(comp<Tin, PZ>((arr)[r], (x)))
 #define W(hh) Storage<Tin>::widen(hh)
@@ -177,6 +168,11 @@ __device__ __forceinline__ void column(const ZPlane<Tin, PZ, RJ> &m, const ZPlan
     for (int r = 0; r < RJ; ++r) {
         const int q = r + 1;
         Tc rsu[PZ], rsv[PZ], rsw[PZ];
+        if constexpr (Epi && !Full) {
+            epi_shift<Tc, PZ>(E.u[r], eshift);
+            epi_shift<Tc, PZ>(E.v[r], eshift);
+            epi_shift<Tc, PZ>(E.w[r], eshift);
+        }
 #pragma unroll
         for (int x = 0; x < PZ; ++x) {
             // su
@@ -235,14 +231,9 @@ __device__ __forceinline__ void column(const ZPlane<Tin, PZ, RJ> &m, const ZPlan
                 store_vec<Tc, PZ>(osv + ooff[r], rsv);
                 store_vec<Tc, PZ>(osw + ooff[r], rsw);
             } else {
-#pragma unroll
-                for (int x = 0; x < PZ; ++x) {
-                    if (x < nvalid) {
-                        PW_GSTORE(Tc, rsu[x], osu + ooff[r] + x * sizeof(Tc));
-                        PW_GSTORE(Tc, rsv[x], osv + ooff[r] + x * sizeof(Tc));
-                        PW_GSTORE(Tc, rsw[x], osw + ooff[r] + x * sizeof(Tc));
-                    }
-                }
+                store_edge<Tc, PZ>(osu + ooff[r], rsu, nvalid);
+                store_edge<Tc, PZ>(osv + ooff[r], rsv, nvalid);
+                store_edge<Tc, PZ>(osw + ooff[r], rsw, nvalid);
             }
         }
     }
@@ -255,8 +246,8 @@ __device__ __forceinline__ void column(const ZPlane<Tin, PZ, RJ> &m, const ZPlan
 // One work item: level chunk tk (64*PZ levels), y-strip ty (RJ rows), marched
 // through x-chunk cx.  All 64 lanes must be active.  Full: the level chunk
 // lies wholly inside the grid ((tk+1)*64*PZ <= nz), so every lane loads
-// whole vectors and owns PZ outputs; otherwise loads are clamped element-wise
-// into the column and each lane stores only its levels inside the grid.
+// owns PZ outputs; otherwise vectors may run past the column's end (see load_row)
+// and each lane stores only its levels inside the grid.
 template <typename Tin, int PZ, int RJ, bool Full, int Depth, bool Epi>
 __device__ __forceinline__ void xmarch(const ZfK<Tin> &a, int tk, int ty, int cx) {
     using Tc = typename Storage<Tin>::Tc;
@@ -280,14 +271,17 @@ __device__ __forceinline__ void xmarch(const ZfK<Tin> &a, int tk, int ty, int cx
         const int hk = (lane & 32) ? min(tk * 64 * PZ + 64 * PZ + a.h, last_k) : tk * 64 * PZ + a.h - 1;
         s.hoff = static_cast<uint32_t>((hrow * a.in_sj + hk) * static_cast<int>(sizeof(Tin)));
     }
-    uint32_t ooff[RJ];
+    s.lim = static_cast<uint32_t>(((prows - 1) * a.in_sj + plev - PZ) * static_cast<int>(sizeof(Tin)));
+    uint32_t ooff[RJ], eoff[RJ];
     bool row_ok[RJ];
     const int kc = min(kk0, a.nz - 1);
+    const uint32_t eshift = epi_off<PZ>(kk0, a.nz);
 #pragma unroll
     for (int r = 0; r < RJ; ++r) {
         row_ok[r] = jj0 + r < a.ny;
         const int jj = min(jj0 + r, a.ny - 1);
         ooff[r] = static_cast<uint32_t>((jj * a.out_sj + kc) * static_cast<int>(sizeof(Tc)));
+        eoff[r] = static_cast<uint32_t>((jj * a.out_sj + epi_col<PZ>(kk0, a.nz)) * static_cast<int>(sizeof(Tc)));
     }
     LaneCoeffs<Tc, PZ> K;
 #pragma unroll
@@ -314,13 +308,13 @@ __device__ __forceinline__ void xmarch(const ZfK<Tin> &a, int tk, int ty, int cx
 #define PW_XLOAD(P, ip)                                                      \
     do {                                                                     \
         if constexpr (Epi) {                                                 \
-            load_zepi<Tin, PZ, RJ, Full>(Ep, a, ii, ooff, kc);               \
+            load_zepi<Tin, PZ, RJ>(Ep, a, ii, eoff);                         \
             __builtin_amdgcn_sched_barrier(0);                               \
         }                                                                    \
         load_xplane<Tin, PZ, RJ, Full>(P, a, min((ip), i1) + h, s, last_k); \
     } while (0)
 #define PW_XPLOAD(P, ip) load_xplane<Tin, PZ, RJ, Full>(P, a, min((ip), i1) + h, s, last_k)
-#define PW_COL(M, C, P) column<Tin, PZ, RJ, Full, Epi>(M, C, P, a, ii, lane0, lane63, nvalid, ooff, row_ok, K, Ep)
+#define PW_COL(M, C, P) column<Tin, PZ, RJ, Full, Epi>(M, C, P, a, ii, lane0, lane63, nvalid, ooff, row_ok, K, Ep, eshift)
     int ii = i0;
     if constexpr (Depth == 1) {
         ZPlane<Tin, PZ, RJ> A, B, C, D;
