@@ -470,7 +470,13 @@ template <int N> __device__ __forceinline__ uint32_t epi_off(int i0, int n) {
 
 // Source terms of output level kk (interior numbering) from planes kk-1 (m),
 // kk (c) and kk+1 (p); stores the lanes/rows that own outputs.
-template <typename Tin, int PX, int RY, bool Full, bool Epi>
+// Epi: what the stores add to alpha * F (0 nothing: out = F).  kEpiLoad: the
+// addends, loaded from their own arrays.  kEpiSelf: the field itself, when the
+// addends are the interior of u, v, w (a time step x + alpha * F(x)): the
+// values are the plane's own centre, already in registers.
+constexpr int kEpiLoad = 1, kEpiSelf = 2;
+
+template <typename Tin, int PX, int RY, bool Full, int Epi>
 __device__ __forceinline__ void level(const Plane<Tin, PX, RY> &m, const Plane<Tin, PX, RY> &c,
                                       const Plane<Tin, PX, RY> &p,
                                       const FwdK<Tin> &a, int kk, bool lane0, bool lane63, int nvalid,
@@ -524,7 +530,7 @@ __device__ __forceinline__ void level(const Plane<Tin, PX, RY> &m, const Plane<T
     for (int r = 0; r < RY; ++r) {
         const int q = r + 1;   // this output row within the loaded rows
         Tc rsu[PX], rsv[PX], rsw[PX];
-        if constexpr (Epi && !Full) {
+        if constexpr (Epi == kEpiLoad && !Full) {
             epi_shift<Tc, PX>(E.u[r], eshift);
             epi_shift<Tc, PX>(E.v[r], eshift);
             epi_shift<Tc, PX>(E.w[r], eshift);
@@ -570,10 +576,15 @@ __device__ __forceinline__ void level(const Plane<Tin, PX, RY> &m, const Plane<T
             sw = fma_(d1 * G(m.w, q, x), hzm, sw);
             sw = fma_(-(d2 * G(p.w, q, x)), hzp, sw);
 
-            if constexpr (Epi) {   // out = c + alpha * F, one rounding
+            // out = c + alpha * F, one rounding
+            if constexpr (Epi == kEpiLoad) {
                 su = fma_(a.alpha, su, comp<Tc, PX>(E.u[r], x));
                 sv = fma_(a.alpha, sv, comp<Tc, PX>(E.v[r], x));
                 sw = fma_(a.alpha, sw, comp<Tc, PX>(E.w[r], x));
+            } else if constexpr (Epi == kEpiSelf) {
+                su = fma_(a.alpha, su, uc);
+                sv = fma_(a.alpha, sv, G(c.v, q, x));
+                sw = fma_(a.alpha, sw, wc);
             }
             rsu[x] = su;
             rsv[x] = sv;
@@ -616,7 +627,7 @@ __device__ __forceinline__ int xcd_tile(int b, int nb) {
 // start of the level, before that level's plane prefetch (a scheduling
 // barrier keeps the compiler from moving them after it), so waiting for them
 // never waits for the prefetch.
-template <typename Tin, int PX, int RY, bool Full, int Depth, bool Epi, int Bc>
+template <typename Tin, int PX, int RY, bool Full, int Depth, int Epi, int Bc>
 __device__ __forceinline__ void strip_march_t(const FwdK<Tin> &a, int tx, int ty, int cz) {
     using Tc = typename Storage<Tin>::Tc;
     const int lane = threadIdx.x & 63;
@@ -687,7 +698,7 @@ __device__ __forceinline__ void strip_march_t(const FwdK<Tin> &a, int tx, int ty
     } while (0)
 #define PW_LOAD(P, kp)                                                   \
     do {                                                                 \
-        if constexpr (Epi) {                                             \
+        if constexpr (Epi == kEpiLoad) {                                 \
             load_epi<Tin, PX, RY>(Ep, a, kk, eoff);                      \
             __builtin_amdgcn_sched_barrier(0);                           \
         }                                                                \
@@ -766,7 +777,7 @@ __device__ __forceinline__ void strip_march_t(const FwdK<Tin> &a, int tx, int ty
 }
 
 // Bc: reads go through the boundary rules a.bcx/bcy/bcz (pw_advect_bc).
-template <typename Tin, int PX, int RY, int Depth, bool Epi = false, int Bc = 0>
+template <typename Tin, int PX, int RY, int Depth, int Epi = 0, int Bc = 0>
 __device__ __forceinline__ void strip_march(const FwdK<Tin> &a, int tx, int ty, int cz) {
     if constexpr (PX == 1) {
         // one-column lanes: loads never need clamping beyond the start column,
@@ -913,7 +924,7 @@ __device__ __forceinline__ void get_edges(const EdgeLds<Tin, PX, W> &L, int slot
 // completed at the two levels before.  Every wavefront of the workgroup runs
 // the same number of levels (same z-chunk), also one whose strip lies past
 // the grid (it loads clamped rows and stores nothing), so the barriers match.
-template <typename Tin, int PX, int RY, bool Full, int Depth, bool Epi, int Bc, int W, int Role, bool NtOwn = false>
+template <typename Tin, int PX, int RY, bool Full, int Depth, int Epi, int Bc, int W, int Role, bool NtOwn = false>
 __device__ __forceinline__ void strip_march_lds_t(const FwdK<Tin> &a, EdgeLds<Tin, PX, W> &L, int tx, int ty,
                                                   int cz, int wave) {
     using Tc = typename Storage<Tin>::Tc;
@@ -976,7 +987,7 @@ __device__ __forceinline__ void strip_march_lds_t(const FwdK<Tin> &a, EdgeLds<Ti
     } while (0)
 #define PW_LOAD(P, kp)                                                   \
     do {                                                                 \
-        if constexpr (Epi) {                                             \
+        if constexpr (Epi == kEpiLoad) {                                 \
             load_epi<Tin, PX, RY>(Ep, a, kk, eoff);                      \
             __builtin_amdgcn_sched_barrier(0);                           \
         }                                                                \
@@ -1056,7 +1067,7 @@ __device__ __forceinline__ void strip_march_lds_t(const FwdK<Tin> &a, EdgeLds<Ti
 // Dispatch of one wavefront of an LDS-sharing workgroup to its role's march
 // (the wave index is wave-uniform, so this branch is taken once, before any
 // load), and to the full-strip or x-edge path.
-template <typename Tin, int PX, int RY, int Depth, bool Epi, int Bc, int W, bool Full, bool NtOwn>
+template <typename Tin, int PX, int RY, int Depth, int Epi, int Bc, int W, bool Full, bool NtOwn>
 __device__ __forceinline__ void strip_march_lds_f(const FwdK<Tin> &a, EdgeLds<Tin, PX, W> &L, int tx, int ty,
                                                   int cz, int wave) {
     static_assert(W >= 2, "sharing needs two wavefronts or more");
@@ -1068,7 +1079,7 @@ __device__ __forceinline__ void strip_march_lds_f(const FwdK<Tin> &a, EdgeLds<Ti
         strip_march_lds_t<Tin, PX, RY, Full, Depth, Epi, Bc, W, kRoleMid, NtOwn>(a, L, tx, ty, cz, wave);
 }
 
-template <typename Tin, int PX, int RY, int Depth, bool Epi, int Bc, int W, bool NtOwn = false>
+template <typename Tin, int PX, int RY, int Depth, int Epi, int Bc, int W, bool NtOwn = false>
 __device__ __forceinline__ void strip_march_lds(const FwdK<Tin> &a, EdgeLds<Tin, PX, W> &L, int tx, int ty, int cz,
                                                 int wave) {
     if constexpr (PX == 1) {

@@ -163,3 +163,38 @@ def test_epilogue_strided_layout_bitwise():
     for d, (b, vw) in zip(dense, outs):
         assert torch.equal(d, vw)
         assert _outside_unchanged(b, d.shape, -4.0)
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (5, 3, 2), (130, 9, 6), (257, 17, 5), (512, 9, 4)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_fields_as_their_own_addends(shape, dtype):
+    """x + alpha * F(x) with the interiors of u, v, w as addends (their values
+    come from the stencil's registers) equals the same call with copies of
+    them (loaded), bit for bit, in every kind of launch shape, with and
+    without boundary rules; a shifted or exchanged addend is loaded."""
+    nx, ny, nz = shape
+    f64 = dtype == np.float64
+    g = wl.make_grid(nx, ny, nz, seed=930 + nx, dtype=dtype)
+    f, c = dev_grid(g)
+    inner = [x[1:-1, 1:-1, 1:-1] for x in f]
+    copies = [x.clone()[1:-1, 1:-1, 1:-1] for x in f]   # equal values, the same strides
+    lid = [("periodic", "periodic", "copy")] * 2 + [("periodic", "periodic", "zero")]
+    tiles = [None, (1, 2, 3, 1, 1, 0), (2, 1, 2, 8, 2, 0), (2, 4, 9, 4, 2, 0)]
+    tiles += [(2, 2, 3, 4, 1, 2)] if f64 else [(4, 1, 2, 4, 1, 2), (4, 2, 9, 2, 1, 2), (4, 2, 3, 4, 1, 1)]
+    swapped = [inner[1], inner[0], inner[2]]
+    for tile in tiles:
+        def run(add, bc):
+            nxt = [torch.full_like(x, 3.5) for x in f]
+            out = tuple(x[1:-1, 1:-1, 1:-1] for x in nxt)
+            if bc is None:
+                B.advect_epilogue(*f, c, add, alpha=0.5, out=out, tile=tile)
+            else:
+                B.advect_bc(*f, c, bc, addends=add, alpha=0.5, out=out, tile=tile)
+            return nxt
+        for bc in (None, lid, ("copy", "copy", "copy")):
+            ref = run(copies, bc)
+            for a, b in zip(run(inner, bc), ref):
+                assert torch.equal(a, b), (tile, bc)
+            for a, b in zip(run(swapped, bc), run([copies[1], copies[0], copies[2]], bc)):
+                assert torch.equal(a, b), (tile, bc)
