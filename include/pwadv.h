@@ -322,8 +322,8 @@ pw_status pw_advect_adjoint_coeff_grad(const pw_grid *grid, const pw_layout *lay
  * environment variable PWADV_TUNE_CACHE names a file, the table is read from
  * it on first use (unreadable or malformed lines are ignored) and the
  * measured entries are rewritten to it after each pw_tune.  Entries measured
- * on MI355X for common shape classes are built in and used when nothing else
- * is known.  fwd_best / adj_best (may be NULL) receive the chosen forward and
+ * on MI355X for some power-of-two grids are built in and used for those grids;
+ * for every other size without an entry a cost rule picks the shape.  fwd_best / adj_best (may be NULL) receive the chosen forward and
  * adjoint shapes (pw_launch_shape reports any kernel's).  Allocates device
  * memory; synchronises its own stream. */
 #define PW_TUNE_FORWARD 1

@@ -136,31 +136,34 @@ bool tile_supported(const TileCfg &c, pw_dtype dt) {
 }
 
 TileCfg default_forward_tile(const FwdArgs &a, pw_dtype dt) {
-    // Measured on MI355X (512x512x64 and 1024x1024x256): four columns per lane
-    // in one-row strips for FP32, two columns in two-row strips for 16-bit
-    // storage, one column in two-row strips for FP64 (register budget); four
-    // strips per workgroup; the march cut into at least two z-chunks, more
-    // when the grid has too few strips for about 8 wavefronts per CU.
-    TileCfg c;
-    c.wpb = 4;
+    // Narrow grids: one column per lane.  Wide ones: 16 bytes per lane with
+    // shared rows -- a short workgroup (two wavefronts of one row, FP32) while
+    // the grid is small enough that wavefronts in flight decide, tall ones
+    // (four wavefronts of two rows, half the rows read twice) where the bytes
+    // do.  Measured, tall against short: 512x512x64 (aligned rows) 69.4 / 82.6
+    // us, 415x420x169 155 / 177, 1000x300x64 106 / 117, but 96.5 / 98.6 at
+    // 536x186x162 and 43.0 / 36.8 (FP32) at half of 250x250x100's levels; FP64
+    // 250x250x100 63 / 69, 201x143x117 46 / 42.
+    const int64_t pts = a.nx * a.ny * a.nz;
     if (dt == PW_F32) {
-        c.px = 4;
-        c.ry = 1;
-    } else if (dt == PW_F64) {
-        c.px = 1;
-        c.ry = 2;
-    } else {
-        c.px = 2;
-        c.ry = 2;
+        static const ShapeCost small[] = {{1, 2, 1, 1, 0, 64, 2048, 0.90}, {1, 4, 1, 1, 0, 64, 2048, 1.50},
+                                          {4, 1, 2, 1, 2, 256, 2048, 0.95}};
+        static const ShapeCost large[] = {{1, 4, 1, 1, 0, 64, 2048, 1.50}, {4, 2, 4, 1, 2, 256, 1024, 1.35}};
+        return pts < 16000000 ? cheapest_shape(small, 3, a.nx, a.ny, a.nz)
+                              : cheapest_shape(large, 2, a.nx, a.ny, a.nz);
     }
-    const int64_t strips = ((a.nx + 64 * c.px - 1) / (64 * c.px)) * ((a.ny + c.ry - 1) / c.ry);
-    int64_t chunks = (2048 + strips - 1) / strips;
-    if (chunks < 2) chunks = 2;
-    int64_t zl = (a.nz + chunks - 1) / chunks;
-    if (zl < 8) zl = 8;
-    if (zl > a.nz) zl = a.nz;
-    c.zlen = static_cast<int>(zl);
-    return c;
+    if (dt == PW_F64) {
+        static const ShapeCost small[] = {{1, 2, 1, 1, 0, 64, 1024, 0.82}, {2, 1, 1, 1, 0, 128, 1024, 0.59},
+                                          {2, 2, 1, 1, 0, 128, 1024, 1.05}};
+        static const ShapeCost large[] = {{1, 4, 1, 1, 0, 64, 1024, 1.30}, {2, 2, 4, 1, 2, 128, 1024, 1.00}};
+        return pts < 5000000 ? cheapest_shape(small, 3, a.nx, a.ny, a.nz)
+                             : cheapest_shape(large, 2, a.nx, a.ny, a.nz);
+    }
+    static const ShapeCost small[] = {{1, 2, 1, 1, 0, 64, 2048, 0.67}, {1, 4, 1, 1, 0, 64, 2048, 1.09},
+                                      {2, 2, 1, 1, 0, 128, 2048, 0.97}, {4, 2, 2, 1, 1, 256, 2048, 1.58}};
+    static const ShapeCost large[] = {{1, 4, 1, 1, 0, 64, 2048, 1.09}, {4, 4, 2, 1, 2, 256, 1024, 2.00}};
+    return pts < 64000000 ? cheapest_shape(small, 4, a.nx, a.ny, a.nz)
+                          : cheapest_shape(large, 2, a.nx, a.ny, a.nz);
 }
 
 pw_status launch_forward(const FwdArgs &a, pw_dtype dt, const TileCfg &cfg, hipStream_t s) {

@@ -97,6 +97,19 @@ struct HaloArgs {
 // consecutive padded columns and the 62 inner lanes own an output each.
 constexpr int kWaveCols = 62;
 
+// A launch shape the rule of pw_shapes.cpp may pick: its tile (without the
+// march length), the columns of one of its strips, the wavefronts of it that
+// the chip holds at once, and its time per level of a full round.
+struct ShapeCost {
+    int px, ry, wpb, depth, share;
+    int cols;
+    int slots;
+    double cost;
+};
+// The cheapest of n shapes, march length included, for a grid of `lead`
+// elements along the lanes, `rows` rows and `march` levels.
+TileCfg cheapest_shape(const ShapeCost *s, int n, int64_t lead, int64_t rows, int64_t march);
+
 bool tile_supported(const TileCfg &c, pw_dtype dt);
 bool adjoint_tile_supported(const TileCfg &c);
 TileCfg default_forward_tile(const FwdArgs &a, pw_dtype dt);

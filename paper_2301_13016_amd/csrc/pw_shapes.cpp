@@ -1,0 +1,58 @@
+// Launch shapes for grids that no tuned entry covers: a cost rule over a few
+// measured shapes.
+//
+// A shape cuts the grid into strips and the march into chunks of z levels;
+// every (strip, chunk) is one wavefront.  The chip holds `slots` wavefronts of
+// the shape at once (1024 SIMDs times the one or two that its registers
+// allow), and a wavefront's time is its levels plus the start of its pipeline
+// (three planes before the first level: about one and a half levels).  So with
+// q = wavefronts / slots the march takes
+//
+//     cost * rounds(q) * (z + 1.5),
+//
+// where whole rounds count one each and a partly filled round counts its
+// share, but at least 0.8: below that the wavefronts in flight no longer
+// saturate the memory and the round is as long as its latency.  `cost` is a
+// shape's time per level of a full round, in arbitrary units, and shapes of
+// different widths compete through their wavefront counts: a strip that a
+// narrow grid half fills costs as much as a full one.
+//
+// The constants are fitted to sweeps over every shape on 46 grids for FP32, 17
+// for FP64 and 16-bit storage, 19 for the z-fastest and the tangent kernels
+// (16 x 16 x 16 to 1024 x 1024 x 64, most of them ragged).  The rule's pick
+// is 2 % (FP32), 2 % (FP64), 1 % (16-bit), 4 % (z-fastest, tangent) slower
+// than the best shape of the sweep in the geometric mean.  The fixed shape with
+// "about 2048 wavefronts, chunks of at least 8 levels" that it replaces was
+// 1.5 to 1.65 times slower than the pick: 9.5 -> 3.5 us at 32x32x64 (chunks
+// of one level: a march of eight is latency, and the grid has too few strips
+// to hide it), 130 -> 48 us at 42x587x244 (one column per lane where four
+// leave 5 lanes in 6 idle), 70 -> 43 us at 300x300x75.
+#include "pw_internal.h"
+
+namespace pw {
+
+TileCfg cheapest_shape(const ShapeCost *s, int n, int64_t lead, int64_t rows, int64_t march) {
+    static const int kChunks[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 128};
+    TileCfg best;
+    double best_cost = -1.0;
+    const int levels = static_cast<int>(march);   // extents are at most 2^30 plus the halo
+    for (int i = 0; i < n; ++i) {
+        const double strips = static_cast<double>((lead + s[i].cols - 1) / s[i].cols) *
+                              static_cast<double>((rows + s[i].ry - 1) / s[i].ry);
+        for (int c : kChunks) {
+            if (c > levels) break;
+            const int z = (levels + c - 1) / c, chunks = (levels + z - 1) / z;
+            const double q = strips * chunks / s[i].slots;
+            const double whole = static_cast<double>(static_cast<int64_t>(q)), part = q - whole;
+            const double rounds = whole + (part > 0.0 ? (part > 0.8 ? part : 0.8) : 0.0);
+            const double cost = s[i].cost * rounds * (z + 1.5);
+            if (best_cost < 0.0 || cost < best_cost) {
+                best_cost = cost;
+                best = TileCfg{s[i].px, s[i].ry, z, s[i].wpb, s[i].depth, s[i].share};
+            }
+        }
+    }
+    return best;
+}
+
+}  // namespace pw

@@ -362,19 +362,13 @@ bool tangent_tile_supported(const TileCfg &c, pw_dtype dt) {
 }
 
 TileCfg default_tangent_tile(const TanArgs &a, pw_dtype dt) {
-    // two-row strips of 64 (FP32: 128) columns, about 2048 wavefronts in flight
-    TileCfg c;
-    c.px = (dt == PW_F64) ? 1 : 2;
-    c.ry = 2;
-    c.wpb = 1;
-    const int64_t strips = ((a.f.nx + 64 * c.px - 1) / (64 * c.px)) * ((a.f.ny + c.ry - 1) / c.ry);
-    int64_t chunks = (2048 + strips - 1) / strips;
-    if (chunks < 1) chunks = 1;
-    int64_t zl = (a.f.nz + chunks - 1) / chunks;
-    if (zl < 8) zl = 8;
-    if (zl > a.f.nz) zl = a.f.nz;
-    c.zlen = static_cast<int>(zl);
-    return c;
+    // two-row strips; FP32: of two columns per lane where the grid fills them
+    if (dt == PW_F64) {
+        static const ShapeCost s[] = {{1, 1, 1, 1, 0, 64, 1024, 0.885}, {1, 2, 1, 1, 0, 64, 1024, 1.55}};
+        return cheapest_shape(s, 2, a.f.nx, a.f.ny, a.f.nz);
+    }
+    static const ShapeCost s[] = {{1, 2, 1, 1, 0, 64, 1024, 0.95}, {2, 2, 1, 1, 0, 128, 1024, 1.57}};
+    return cheapest_shape(s, 2, a.f.nx, a.f.ny, a.f.nz);
 }
 
 pw_status launch_tangent(const TanArgs &a, pw_dtype dt, const TileCfg &cfg, hipStream_t s) {

@@ -238,6 +238,11 @@ bool lookup_tuned(TuneKind kind, const pw_grid *grid, pw_dtype dt, TileCfg *cfg)
     load_locked();
     auto it = g_table.find(make_key(kind, grid, dt));
     if (it == g_table.end()) return false;
+    // A built-in entry holds for the power-of-two grid it was measured on (aligned rows, whole strips); other
+    // sizes of its class are better served by the cost rule: 201x143x117 FP32 29 us with the entry of
+    // 256x256x128, 19 us with the rule's shape.
+    auto power = [](int64_t n) { return (n & (n - 1)) == 0; };
+    if (!it->second.measured && !(power(grid->nx) && power(grid->ny) && power(grid->nz))) return false;
     *cfg = entry_to_cfg(it->second, march_extent(kind, grid));
     switch (kind) {
         case TuneKind::Forward: return tile_supported(*cfg, dt);
