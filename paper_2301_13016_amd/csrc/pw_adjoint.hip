@@ -14,14 +14,35 @@
 //
 // Layout and launch mirror the forward kernel: a wavefront owns a strip of 62
 // padded columns x RY padded rows and marches through padded z-levels with a
-// four-plane register ring (values u, v, w and cotangents of planes k-1, k,
-// k+1 feed level k while k+2 is in flight); x-neighbours come from DPP
-// wavefront shifts.  Cotangents outside the interior read as 0.  Values in
-// cells that no output reads (3-D halo corners, most halo edges, every cell
-// beyond the first halo layer, and positions outside the padded array, which
-// are loaded from the nearest valid entry) read as 0 as well: they only ever
-// meet zero cotangents, and zeroing them keeps a non-finite value there
-// (0 * NaN = NaN) out of the gradient.
+// register ring of planes k, k+1 (values u, v, w and cotangents) and k+2 in
+// flight; what level k needs of plane k-1 is carried over as the terms that
+// level k-1 formed of it (Carry), so no term is computed twice and no third
+// plane is kept.  x-neighbours come from DPP wavefront shifts.
+//
+// Cotangents outside the interior read as 0, and so do values in cells that
+// no output reads (3-D halo corners, most halo edges, every cell beyond the
+// first halo layer, positions outside the padded array): they only ever meet
+// zero cotangents, and a 0 keeps a non-finite value there (0 * NaN = NaN) out
+// of the gradient.  Loads go through buffer descriptors, where an offset past
+// the range reads 0 without touching memory: cotangents outside the interior
+// and values that no plane's outputs read are given such an offset once per
+// strip, planes outside the interior an empty range.  What depends on plane,
+// row and column together is put out of range plane by plane, in strips and
+// planes at the grid's surface (a wave-uniform test); rows and columns that
+// own no gradient store out of range.  So no load is waited for and no store
+// is branched around before its time, which is what counts where a strip has
+// a SIMD to itself: 200x200x80 in 408 strips of 44 levels 66 us with selects
+// and branches, 53 us.
+//
+// What bounds it: 6 arrays read and 3 written in rows whose pitch (nx + 2h) is
+// no multiple of a cache line.  The same accesses with trivial arithmetic run
+// no faster than the kernel (256x256x128 FP32: 75 us), without the stores 44
+// us; half the lines of a 62-column piece are shared with the next strip.
+// Strips next to each other in x therefore run on one XCD at the same time
+// (tiles are numbered x fastest), so that its L2 merges the parts of a line:
+// z-chunk fastest 82.6 us, x fastest 77.4; six z-chunks 96.8 and 85.1.  The
+// carried terms count where arithmetic is added to the same accesses: wind and
+// coefficient gradients in one pass over 512x512x64 226 us before, 208 now.
 #include "pw_internal.h"
 #include "pw_lanes.h"
 #include "pw_reduce.h"
@@ -69,10 +90,14 @@ template <typename T, int RY> struct APlane {
 constexpr uint32_t kCotOk = 1u << 12;
 
 template <typename T, int RY> struct StripAddr {
-    uint32_t voff[RY + 2];   // byte offsets of the value rows (clamped)
-    uint32_t roff[RY + 2];   // byte offsets of the cotangent rows (clamped)
+    uint32_t voff[RY + 2];   // byte offsets of the value rows (kOutside: never read)
+    uint32_t roff[RY + 2];   // byte offsets of the cotangent rows (kOutside: none there)
     uint32_t mask[RY + 2];   // per row, see kCotOk
+    int corner;              // the strip reaches the x and the y halo (wave-uniform)
 };
+
+// An offset past every plane's range (planes are below 2 GiB): reads 0.
+constexpr uint32_t kOutside = 0x80000000u;
 
 // Position class of a padded coordinate x along an axis with interior
 // [h, h + n): 0 interior, 1 the halo layer just below it, 2 the layer just
@@ -123,27 +148,43 @@ template <typename T> __device__ __forceinline__ void bstore(T x, __amdgpu_buffe
 template <typename T, int RY>
 __device__ __forceinline__ void load_aplane(APlane<T, RY> &P, const AdjK<T> &a, int kp, const StripAddr<T, RY> &s) {
     const int pz = a.nz + 2 * a.h;
+    const bool in = kp >= 0 && kp < pz;
+    // (readfirstlane: what depends on the class must stay scalar, or every
+    // load loops over the lanes' descriptors)
+    P.kcls = __builtin_amdgcn_readfirstlane(pos_class(kp, a.h, a.nz));
     const int kv = min(max(kp, 0), pz - 1);
     const int64_t pb = static_cast<int64_t>(kv) * a.in_sz * static_cast<int64_t>(sizeof(T));
-    const int64_t vbytes = a.in_sz * static_cast<int64_t>(sizeof(T));
+    const int64_t vbytes = in ? a.in_sz * static_cast<int64_t>(sizeof(T)) : 0;
     const auto bu = plane_rsrc(reinterpret_cast<const char *>(a.u) + pb, vbytes);
     const auto bv = plane_rsrc(reinterpret_cast<const char *>(a.v) + pb, vbytes);
     const auto bw = plane_rsrc(reinterpret_cast<const char *>(a.w) + pb, vbytes);
+    uint32_t ou[RY + 2], ov[RY + 2], ow[RY + 2];
+#pragma unroll
+    for (int r = 0; r < RY + 2; ++r) ou[r] = ov[r] = ow[r] = s.voff[r];
+    if ((s.corner | P.kcls) != 0) {
+        // cells that no output reads on a plane of this class: on interior
+        // planes only the halo edges where the x and the y halo meet, on the
+        // two z-halo planes everything in the x or y halo.  Masked through
+        // the offsets: a select on the loaded values would wait for them.
+#pragma unroll
+        for (int r = 0; r < RY + 2; ++r) {
+            const uint32_t unread = ~(s.mask[r] >> (3 * P.kcls));
+            ou[r] |= unread << 31;
+            ov[r] |= (unread >> 1) << 31;
+            ow[r] |= (unread >> 2) << 31;
+        }
+    }
 #pragma unroll
     for (int r = 0; r < RY + 2; ++r) {
-        P.u[r] = bload<T>(bu, s.voff[r]);
-        P.v[r] = bload<T>(bv, s.voff[r]);
-        P.w[r] = bload<T>(bw, s.voff[r]);
+        P.u[r] = bload<T>(bu, ou[r]);
+        P.v[r] = bload<T>(bv, ov[r]);
+        P.w[r] = bload<T>(bw, ow[r]);
     }
-    // Cotangents: every load from a clamped (valid) address and without a
-    // branch, so that the plane's loads stay in flight until its first use,
-    // where mask_aplane zeroes what lies outside the interior.
     const int kk = kp - a.h;
     P.zok = kk >= 0 && kk < a.nz;
-    P.kcls = (kp < 0 || kp >= pz) ? 3 : pos_class(kp, a.h, a.nz);
     const int kc = min(max(kk, 0), a.nz - 1);
     const int64_t ob = static_cast<int64_t>(kc) * a.out_sz * static_cast<int64_t>(sizeof(T));
-    const int64_t obytes = a.out_sz * static_cast<int64_t>(sizeof(T));
+    const int64_t obytes = P.zok ? a.out_sz * static_cast<int64_t>(sizeof(T)) : 0;
     const auto cu = plane_rsrc(reinterpret_cast<const char *>(a.ru) + ob, obytes);
     const auto cv = plane_rsrc(reinterpret_cast<const char *>(a.rv) + ob, obytes);
     const auto cw = plane_rsrc(reinterpret_cast<const char *>(a.rw) + ob, obytes);
@@ -155,23 +196,6 @@ __device__ __forceinline__ void load_aplane(APlane<T, RY> &P, const AdjK<T> &a, 
     }
 }
 
-// Zero the cotangents of a loaded plane outside the interior, and the values
-// of cells no output reads (once per plane, at its first use).
-template <typename T, int RY>
-__device__ __forceinline__ void mask_aplane(APlane<T, RY> &P, const StripAddr<T, RY> &s) {
-#pragma unroll
-    for (int r = 0; r < RY + 2; ++r) {
-        const bool ok = P.zok && (s.mask[r] & kCotOk);
-        P.ru[r] = ok ? P.ru[r] : T(0);
-        P.rv[r] = ok ? P.rv[r] : T(0);
-        P.rw[r] = ok ? P.rw[r] : T(0);
-        const uint32_t rd = s.mask[r] >> (3 * P.kcls);
-        P.u[r] = (rd & 1u) ? P.u[r] : T(0);
-        P.v[r] = (rd & 2u) ? P.v[r] : T(0);
-        P.w[r] = (rd & 4u) ? P.w[r] : T(0);
-    }
-}
-
 // Coefficient at a wave-uniform level, as a scalar load through the constant
 // address space (the library rejects gradients that overlap the coefficient
 // arrays); clamped: only ever met by a zero cotangent when outside.
@@ -179,16 +203,48 @@ template <typename T> __device__ __forceinline__ T coef(const T *c, int kk, int 
     return ((const __attribute__((address_space(4))) T *)(c))[min(max(kk, 0), nz - 1)];
 }
 
-// Gradients at padded level kp from planes kp-1 (m), kp (c), kp+1 (p).
+// What level k+1 needs of plane k (its plane below): per own row of the strip
+// the terms of the gradients that plane k's values and cotangents form among
+// themselves, and for the coefficient partials plane k's values.  Formed once,
+// at level k, which uses the first four itself.
+template <typename T, int RY> struct Carry {
+    T xw[RY], yw[RY];   // rw(i+1) w(i) - rw(i) w(i+1), and the same in y
+    T fz[RY], gz[RY];   // w(i) + w(i+1), w(j) + w(j+1)
+    T au[RY], av[RY];   // tzc2 ru fz, tzc2 rv gz: the upper z-faces of su, sv
+    T dw[RY];           // tzd2 rw
+    T u[RY], v[RY], w[RY];
+};
+
 template <typename T, int RY>
-__device__ __forceinline__ void adj_level(const APlane<T, RY> &m, const APlane<T, RY> &c, APlane<T, RY> &p,
-                                          const AdjK<T> &a, const StripAddr<T, RY> &s, int kp, bool lane_ok,
-                                          const uint32_t (&goff)[RY], const bool (&row_ok)[RY]) {
+__device__ __forceinline__ void carry_of(Carry<T, RY> &C, const APlane<T, RY> &c, const AdjK<T> &a, int kp) {
+    const T c2 = coef(a.tzc2, kp - a.h, a.nz), d2 = coef(a.tzd2, kp - a.h, a.nz);
+#pragma unroll
+    for (int r = 0; r < RY; ++r) {
+        const int q = r + 1;
+        const T w_r = from_right(c.w[q]);
+        C.xw[r] = fma_(from_right(c.rw[q]), c.w[q], -(c.rw[q] * w_r));
+        C.yw[r] = fma_(c.rw[q + 1], c.w[q], -(c.rw[q] * c.w[q + 1]));
+        C.fz[r] = c.w[q] + w_r;
+        C.gz[r] = c.w[q] + c.w[q + 1];
+        C.au[r] = c2 * c.ru[q] * C.fz[r];
+        C.av[r] = c2 * c.rv[q] * C.gz[r];
+        C.dw[r] = d2 * c.rw[q];
+        C.u[r] = c.u[q];
+        C.v[r] = c.v[q];
+        C.w[r] = c.w[q];
+    }
+}
+
+// Gradients at padded level kp from plane kp (c; its own terms in n), plane
+// kp+1 (p) and the terms carried from plane kp-1 (m).
+template <typename T, int RY>
+__device__ __forceinline__ void adj_level(const Carry<T, RY> &m, const Carry<T, RY> &n, const APlane<T, RY> &c,
+                                          const APlane<T, RY> &p, const AdjK<T> &a, int kp,
+                                          const uint32_t (&goff)[RY]) {
     const int kq = kp - a.h;   // interior level index of this gradient plane
     const T tcx = a.tcx, tcy = a.tcy;
-    const T c1p = coef(a.tzc1, kq + 1, a.nz), c2m = coef(a.tzc2, kq - 1, a.nz), c2 = coef(a.tzc2, kq, a.nz);
-    const T d1 = coef(a.tzd1, kq, a.nz), d2 = coef(a.tzd2, kq, a.nz);
-    const T d2m = coef(a.tzd2, kq - 1, a.nz), d1p = coef(a.tzd1, kq + 1, a.nz);
+    const T c1p = coef(a.tzc1, kq + 1, a.nz), c2 = coef(a.tzc2, kq, a.nz);
+    const T d1 = coef(a.tzd1, kq, a.nz), d2 = coef(a.tzd2, kq, a.nz), d1p = coef(a.tzd1, kq + 1, a.nz);
 
     // Row-shared pieces (index r = loaded row r):
     //   xv[r] = rv(r,i+1) v(r,i) - rv(r,i) v(r,i+1)          plane k   (gu: sv x-terms)
@@ -224,14 +280,11 @@ __device__ __forceinline__ void adj_level(const APlane<T, RY> &m, const APlane<T
         gx = fma_(c.ru[q], u_l - u_r, gx);
         gx = fma_(-ru_l, fma_(two, c.u[q], u_l), gx);
         // sv and sw x-terms: antisymmetric pairs at rows j-1, j (sv) and planes k-1, k (sw)
-        const T xw_c = fma_(from_right(c.rw[q]), c.w[q], -(c.rw[q] * from_right(c.w[q])));
-        const T xw_m = fma_(from_right(m.rw[q]), m.w[q], -(m.rw[q] * from_right(m.w[q])));
-        gx = gx + ((xv[r] + xv[q]) + (xw_m + xw_c));
+        gx = gx + ((xv[r] + xv[q]) + (m.xw[r] + n.xw[r]));
         // su y-terms
         const T gyu = fma_(c.ru[q + 1], fy[q], -(c.ru[q - 1] * fy[r]));
         // su z-terms
-        const T gzu = fma_(c1p * p.ru[q], c.w[q] + from_right(c.w[q]),
-                           -(c2m * m.ru[q] * (m.w[q] + from_right(m.w[q]))));
+        const T gzu = fma_(c1p * p.ru[q], n.fz[r], -m.au[r]);
         T gu = tcx * gx;
         gu = fma_(tcy, gyu, gu);
         gu = gu + gzu;
@@ -248,12 +301,10 @@ __device__ __forceinline__ void adj_level(const APlane<T, RY> &m, const APlane<T
         gyv = fma_(c.rv[q], c.v[q - 1] - c.v[q + 1], gyv);
         gyv = fma_(-c.rv[q - 1], fma_(two, c.v[q], c.v[q - 1]), gyv);
         // sw y-terms at planes k-1 and k: yw = rw(j+1) w(j) - rw(j) w(j+1)
-        const T yw_c = fma_(c.rw[q + 1], c.w[q], -(c.rw[q] * c.w[q + 1]));
-        const T yw_m = fma_(m.rw[q + 1], m.w[q], -(m.rw[q] * m.w[q + 1]));
         // sv z-terms
-        const T gzv = fma_(c1p * p.rv[q], c.w[q] + c.w[q + 1], -(c2m * m.rv[q] * (m.w[q] + m.w[q + 1])));
+        const T gzv = fma_(c1p * p.rv[q], n.gz[r], -m.av[r]);
         T gv = tcx * gxv;
-        gv = fma_(tcy, (gyv_su + gyv) + (yw_m + yw_c), gv);
+        gv = fma_(tcy, (gyv_su + gyv) + (m.yw[r] + n.yw[r]), gv);
         gv = gv + gzv;
 
         // ---------------------------------------------------------------- gw
@@ -261,8 +312,8 @@ __device__ __forceinline__ void adj_level(const APlane<T, RY> &m, const APlane<T
         const T zu = fma_(c1p * p.ru[q], c.u[q], -(c2 * c.ru[q] * p.u[q]));
         // sw z-terms
         T gzw = d1p * p.rw[q] * fma_(two, c.w[q], p.w[q]);
-        gzw = fma_(c.rw[q], fma_(d1, m.w[q], -(d2 * p.w[q])), gzw);
-        gzw = fma_(-(d2m * m.rw[q]), fma_(two, c.w[q], m.w[q]), gzw);
+        gzw = fma_(c.rw[q], fma_(d1, m.w[r], -(d2 * p.w[q])), gzw);
+        gzw = fma_(-m.dw[r], fma_(two, c.w[q], m.w[r]), gzw);
         // sw x-terms
         const T hxu = c.u[q] + p.u[q];   // u(k,i) + u(k+1,i)
         const T gxw = fma_(from_right(c.rw[q]), hxu, -(from_left(c.rw[q]) * from_left(hxu)));
@@ -273,11 +324,10 @@ __device__ __forceinline__ void adj_level(const APlane<T, RY> &m, const APlane<T
         gw = fma_(tcx, gxw, gw);
         gw = fma_(tcy, gyw, gw);
 
-        if (lane_ok && row_ok[r]) {
-            bstore<T>(gu, ogu, goff[r]);
-            bstore<T>(gv, ogv, goff[r]);
-            bstore<T>(gw, ogw, goff[r]);
-        }
+        // lanes and rows that own no gradient have an offset past the range
+        bstore<T>(gu, ogu, goff[r]);
+        bstore<T>(gv, ogv, goff[r]);
+        bstore<T>(gw, ogw, goff[r]);
     }
 }
 
@@ -295,9 +345,9 @@ __device__ __forceinline__ void adj_level(const APlane<T, RY> &m, const APlane<T
 // NaN there would survive).
 constexpr int kQ = 6;
 template <typename T, int RY>
-__device__ __forceinline__ void cg_level(const APlane<T, RY> &m, const APlane<T, RY> &c, const APlane<T, RY> &p,
-                                         const AdjK<T> &a, const StripAddr<T, RY> &s, int kp, bool lane_ok,
-                                         int strip) {
+__device__ __forceinline__ void cg_level(const Carry<T, RY> &m, const Carry<T, RY> &n, const APlane<T, RY> &c,
+                                         const APlane<T, RY> &p, const AdjK<T> &a, const StripAddr<T, RY> &s, int kp,
+                                         bool lane_ok, int strip) {
     if (!c.zok) return;   // a halo level (wave-uniform)
     T fy[RY + 1];
 #pragma unroll
@@ -312,19 +362,19 @@ __device__ __forceinline__ void cg_level(const APlane<T, RY> &m, const APlane<T,
         const T uc = c.u[q], ul = from_left(c.u[q]), ur = from_right(c.u[q]);
         const T ax = fma_(-ur, uc + ur, ul * (uc + ul));
         const T ay = fma_(-c.u[q + 1], fy[q], c.u[q - 1] * fy[r]);
-        const T az1 = m.u[q] * (m.w[q] + from_right(m.w[q]));
-        const T az2 = p.u[q] * (c.w[q] + from_right(c.w[q]));
+        const T az1 = m.u[r] * m.fz[r];
+        const T az2 = p.u[q] * n.fz[r];
         // sv term groups
         const T vc = c.v[q], vl = from_left(c.v[q]), vr = from_right(c.v[q]);
         const T bx = fma_(-vr, uc + c.u[q + 1], vl * (ul + from_left(c.u[q + 1])));
         const T by = fma_(-c.v[q + 1], vc + c.v[q + 1], c.v[q - 1] * (vc + c.v[q - 1]));
-        const T bz1 = m.v[q] * (m.w[q] + m.w[q + 1]);
-        const T bz2 = p.v[q] * (c.w[q] + c.w[q + 1]);
+        const T bz1 = m.v[r] * m.gz[r];
+        const T bz2 = p.v[q] * n.gz[r];
         // sw term groups
         const T wc = c.w[q], wl = from_left(c.w[q]), wr = from_right(c.w[q]);
         const T cx = fma_(-wr, uc + p.u[q], wl * (ul + from_left(p.u[q])));
         const T cy = fma_(-c.w[q + 1], c.v[q] + p.v[q], c.w[q - 1] * (c.v[q - 1] + p.v[q - 1]));
-        const T cz1 = m.w[q] * (wc + m.w[q]);
+        const T cz1 = m.w[r] * (wc + m.w[r]);
         const T cz2 = p.w[q] * (wc + p.w[q]);
         sq[0] += ok ? fma_(ra, az1, rb * bz1) : T(0);
         sq[1] -= ok ? fma_(ra, az2, rb * bz2) : T(0);
@@ -350,7 +400,7 @@ __device__ __forceinline__ int xcd_tile(int b, int nb) {
     return x * q + min(x, rem) + i;
 }
 
-// Depth: planes in flight ahead of the three a level reads (1 or 2).
+// Depth: planes in flight ahead of the two a level reads (1 or 2).
 // MaxT: workgroup size bound (built for 256 and 512 threads; see the forward
 // kernel).
 template <typename T, int RY, int Depth, int MaxT, int Mode>
@@ -359,15 +409,14 @@ __global__ __launch_bounds__(MaxT) void pw_adjoint_kernel(AdjK<T> a) {
     // wavefront index as a scalar, so that per-strip conditions stay scalar
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int t = xcd_tile(blockIdx.x, gridDim.x);
-    const int cz = t % a.nzc;
-    const int t2 = t / a.nzc;
-    const int tx = t2 % a.ntx;
-    const int ty = (t2 / a.ntx) * a.wpb + wave;
+    const int tx = t % a.ntx;   // x fastest: neighbours share cache lines of every row they store
+    const int t2 = t / a.ntx;
+    const int cz = t2 % a.nzc;
+    const int ty = (t2 / a.nzc) * a.wpb + wave;
     if (ty >= a.nty) return;
 
     const int px = a.nx + 2 * a.h, py = a.ny + 2 * a.h, pz = a.nz + 2 * a.h;
     const int pcol = tx * kWaveCols - 1 + lane;        // padded column loaded by this lane
-    const int vcol = min(max(pcol, 0), px - 1);
     const int icol = pcol - a.h;                        // its interior column
     const bool lane_ok = lane >= 1 && lane <= kWaveCols && pcol < px;
     const int jb = ty * RY;                             // first padded gradient row
@@ -375,14 +424,16 @@ __global__ __launch_bounds__(MaxT) void pw_adjoint_kernel(AdjK<T> a) {
     StripAddr<T, RY> s;
     const bool rcol = icol >= 0 && icol < a.nx;
     const int icls = (pcol < 0 || pcol >= px) ? 3 : pos_class(pcol, a.h, a.nx);
-    const int icl = min(max(icol, 0), a.nx - 1);
+    bool yhalo = false;
 #pragma unroll
     for (int r = 0; r < RY + 2; ++r) {
         const int prow = jb - 1 + r;
-        const int vr = min(max(prow, 0), py - 1);
-        s.voff[r] = static_cast<uint32_t>((vr * a.in_sy + vcol) * static_cast<int>(sizeof(T)));
         const int ir = prow - a.h;
         const int jcls = (prow < 0 || prow >= py) ? 3 : pos_class(prow, a.h, a.ny);
+        s.voff[r] = (jcls == 3 || icls == 3)
+                        ? kOutside
+                        : static_cast<uint32_t>((prow * a.in_sy + pcol) * static_cast<int>(sizeof(T)));
+        yhalo = yhalo || jcls != 0;
         uint32_t m = (rcol && ir >= 0 && ir < a.ny) ? kCotOk : 0u;
 #pragma unroll
         for (int kc = 0; kc < 4; ++kc) {
@@ -393,79 +444,73 @@ __global__ __launch_bounds__(MaxT) void pw_adjoint_kernel(AdjK<T> a) {
             m |= (read_w ? 4u : 0u) << (3 * kc);
         }
         s.mask[r] = m;
-        const int irc = min(max(ir, 0), a.ny - 1);
-        s.roff[r] = static_cast<uint32_t>((irc * a.out_sy + icl) * static_cast<int>(sizeof(T)));
+        s.roff[r] = (m & kCotOk) ? static_cast<uint32_t>((ir * a.out_sy + icol) * static_cast<int>(sizeof(T))) : kOutside;
     }
+    const bool xhalo = __ballot(icls != 0) != 0;
+    s.corner = __builtin_amdgcn_readfirstlane(xhalo && yhalo ? 1 : 0);
     uint32_t goff[RY];
-    bool row_ok[RY];
 #pragma unroll
-    for (int r = 0; r < RY; ++r) {
-        row_ok[r] = jb + r < py;
-        const int gr = min(jb + r, py - 1);
-        goff[r] = static_cast<uint32_t>((gr * a.in_sy + vcol) * static_cast<int>(sizeof(T)));
-    }
+    for (int r = 0; r < RY; ++r)
+        goff[r] = (lane_ok && jb + r < py)
+                      ? static_cast<uint32_t>(((jb + r) * a.in_sy + pcol) * static_cast<int>(sizeof(T)))
+                      : kOutside;
 
     const int k0 = cz * a.zlen;
     const int k1 = min(pz, k0 + a.zlen);
+    const int strip = ty * a.ntx + tx;
     // Unconditional prefetch (past the chunk's last level it re-reads plane
     // k1, a cache hit, into a slot no level uses): a conditional load would
     // join two paths with different loads in flight, and the wait at the join
     // drains the prefetch.
-    const int strip = ty * a.ntx + tx;
-#define PW_ALEVEL(M, C, P)                                                                    \
-    do {                                                                                      \
-        mask_aplane<T, RY>(P, s);   /* first use of plane k+1 */                              \
-        if constexpr (Mode & kModeGrad) adj_level<T, RY>(M, C, P, a, s, k, lane_ok, goff, row_ok); \
-        if constexpr (Mode & kModeCg) cg_level<T, RY>(M, C, P, a, s, k, lane_ok, strip);           \
+#define PW_ALEVEL(C, P)                                                                                \
+    do {                                                                                               \
+        Carry<T, RY> n;                                                                                \
+        carry_of<T, RY>(n, C, a, k);                                                                   \
+        if constexpr (Mode & kModeGrad) adj_level<T, RY>(m, n, C, P, a, k, goff);                      \
+        if constexpr (Mode & kModeCg) cg_level<T, RY>(m, n, C, P, a, s, k, lane_ok, strip);            \
+        m = n;                                                                                         \
     } while (0)
     int k = k0;
+    Carry<T, RY> m;   // of plane k-1
     if constexpr (Depth == 1) {
-        // four-plane ring: planes k-1, k, k+1 feed level k, k+2 in flight
-        APlane<T, RY> A, B, C, D;
-        load_aplane<T, RY>(A, a, k0 - 1, s);
-        load_aplane<T, RY>(B, a, k0, s);
-        load_aplane<T, RY>(C, a, k0 + 1, s);
-        mask_aplane<T, RY>(A, s);
-        mask_aplane<T, RY>(B, s);
+        // three-plane ring: planes k, k+1 feed level k, k+2 in flight
+        APlane<T, RY> A, B, C;
+        load_aplane<T, RY>(C, a, k0 - 1, s);
+        load_aplane<T, RY>(A, a, k0, s);
+        load_aplane<T, RY>(B, a, k0 + 1, s);
+        carry_of<T, RY>(m, C, a, k0 - 1);
         for (;;) {
-            load_aplane<T, RY>(D, a, min(k + 2, k1), s);
-            PW_ALEVEL(A, B, C);
+            load_aplane<T, RY>(C, a, min(k + 2, k1), s);
+            PW_ALEVEL(A, B);
             if (++k >= k1) break;
             load_aplane<T, RY>(A, a, min(k + 2, k1), s);
-            PW_ALEVEL(B, C, D);
+            PW_ALEVEL(B, C);
             if (++k >= k1) break;
             load_aplane<T, RY>(B, a, min(k + 2, k1), s);
-            PW_ALEVEL(C, D, A);
-            if (++k >= k1) break;
-            load_aplane<T, RY>(C, a, min(k + 2, k1), s);
-            PW_ALEVEL(D, A, B);
+            PW_ALEVEL(C, A);
             if (++k >= k1) break;
         }
     } else {
-        // five-plane ring: planes k+2 and k+3 in flight
+        // four-plane ring: planes k+2 and k+3 in flight
         static_assert(Depth == 2, "prefetch depth 1 or 2");
-        APlane<T, RY> A, B, C, D, E;
-        load_aplane<T, RY>(A, a, k0 - 1, s);
-        load_aplane<T, RY>(B, a, k0, s);
-        load_aplane<T, RY>(C, a, k0 + 1, s);
-        load_aplane<T, RY>(D, a, min(k0 + 2, k1), s);
-        mask_aplane<T, RY>(A, s);
-        mask_aplane<T, RY>(B, s);
+        APlane<T, RY> A, B, C, D;
+        load_aplane<T, RY>(D, a, k0 - 1, s);
+        load_aplane<T, RY>(A, a, k0, s);
+        load_aplane<T, RY>(B, a, k0 + 1, s);
+        load_aplane<T, RY>(C, a, min(k0 + 2, k1), s);
+        carry_of<T, RY>(m, D, a, k0 - 1);
         for (;;) {
-            load_aplane<T, RY>(E, a, min(k + 3, k1), s);
-            PW_ALEVEL(A, B, C);
+            load_aplane<T, RY>(D, a, min(k + 3, k1), s);
+            PW_ALEVEL(A, B);
             if (++k >= k1) break;
             load_aplane<T, RY>(A, a, min(k + 3, k1), s);
-            PW_ALEVEL(B, C, D);
+            PW_ALEVEL(B, C);
             if (++k >= k1) break;
             load_aplane<T, RY>(B, a, min(k + 3, k1), s);
-            PW_ALEVEL(C, D, E);
+            PW_ALEVEL(C, D);
             if (++k >= k1) break;
             load_aplane<T, RY>(C, a, min(k + 3, k1), s);
-            PW_ALEVEL(D, E, A);
-            if (++k >= k1) break;
-            load_aplane<T, RY>(D, a, min(k + 3, k1), s);
-            PW_ALEVEL(E, A, B);
+            PW_ALEVEL(D, A);
             if (++k >= k1) break;
         }
     }
