@@ -603,21 +603,29 @@ bool adjoint_tile_supported(const TileCfg &c) {
 }
 
 TileCfg default_adjoint_tile(const AdjArgs &a, pw_dtype dt) {
-    // Measured on MI355X (256x256x128 FP32): two-row strips, one wavefront
-    // per workgroup, about 2048 wavefronts in flight.
-    TileCfg c;
-    c.px = 1;
-    c.ry = (dt == PW_F64) ? 1 : 2;
-    c.wpb = 1;
-    const int64_t px = a.nx + 2 * a.h, py = a.ny + 2 * a.h, pz = a.nz + 2 * a.h;
-    const int64_t strips = ((px + kWaveCols - 1) / kWaveCols) * ((py + c.ry - 1) / c.ry);
-    int64_t chunks = (2048 + strips - 1) / strips;
-    if (chunks < 2) chunks = 2;
-    int64_t zl = (pz + chunks - 1) / chunks;
-    if (zl < 8) zl = 8;
-    if (zl > pz) zl = pz;
-    c.zlen = static_cast<int>(zl);
-    return c;
+    // Two- and four-row strips, one wavefront per workgroup (several share no
+    // data and end together: 2 to 10 % slower), one plane ahead.  Fitted to 18
+    // grids for FP32 and 9 for FP64; the pick is 2 % (FP32) and 3 % (FP64)
+    // slower than the best shape of the sweep.  Against "about 2048
+    // wavefronts" of two rows (FP64: one): 32x32x64 9.6 -> 5.7 us,
+    // 250x250x100 68.8 -> 62.3 and FP64 139 -> 117, 42x587x244 77 -> 60.
+    (void)dt;
+    static const ShapeCost s[] = {{1, 2, 1, 1, 0, kWaveCols, 1024, 1.0}, {1, 4, 1, 1, 0, kWaveCols, 1024, 1.6}};
+    return cheapest_shape(s, 2, a.nx + 2 * a.h, a.ny + 2 * a.h, a.nz + 2 * a.h, 2.5);
+}
+
+TileCfg coeff_grad_tile(const pw_grid &g, pw_dtype dt) {
+    // Fitted to both passes over the same grids: 2 % slower than the best
+    // shape.  FP32 keeps four rows, which a lane sums in FP32 before the FP64
+    // sums (other strips would round the partials otherwise), and holds two
+    // wavefronts per SIMD; with FP64's registers a second one adds nothing.
+    // Against four rows (FP64: one) in one round of 2048 wavefronts and at
+    // least eight levels, with the wind gradients: 32x32x64 23.2 -> 12.8 us,
+    // 512x512x32 109.5 -> 103, FP64 250x250x100 172 -> 130.
+    static const ShapeCost f32[] = {{1, 4, 1, 1, 0, kWaveCols, 2048, 1.0}};
+    static const ShapeCost f64[] = {{1, 2, 1, 1, 0, kWaveCols, 1024, 1.0}, {1, 4, 1, 1, 0, kWaveCols, 1024, 1.6}};
+    return cheapest_shape(dt == PW_F64 ? f64 : f32, dt == PW_F64 ? 2 : 1, g.nx + 2 * g.halo, g.ny + 2 * g.halo,
+                          g.nz + 2 * g.halo, 2.5);
 }
 
 int64_t adjoint_strips(const pw_grid &g, int ry) {

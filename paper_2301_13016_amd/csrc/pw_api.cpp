@@ -584,34 +584,6 @@ pw_status check_coeff_grad(const pw_grid *grid, const pw_layout *layout, pw_dtyp
 namespace pw {
 namespace {
 
-// Launch shape of every coefficient-gradient pass, fixed by the grid's size
-// alone, so that the partials -- and the gradients -- are the same bit for
-// bit whether the wind gradients are computed with them or not.  Measured on
-// MI355X (256x256x128 FP32, the three adjoint modes over rows per strip,
-// z-chunks, wavefronts per workgroup and prefetch depth): four-row strips
-// (FP64: one row, for registers), one wavefront per workgroup, and the march
-// cut into as many z-chunks as keep the wavefronts within one round of the
-// chip's 2048 slots (these kernels hold about 220 VGPRs: two wavefronts per
-// SIMD).  One round more with a short tail costs a quarter: 2275 wavefronts
-// took 139 us where 1950 took 113 us.
-TileCfg coeff_grad_tile(const pw_grid *grid, pw_dtype dtype) {
-    TileCfg c;
-    c.px = 1;
-    c.ry = dtype == PW_F64 ? 1 : 4;
-    c.wpb = 1;
-    c.depth = 1;
-    c.share = 0;
-    const int64_t pz = grid->nz + 2 * grid->halo;
-    const int64_t strips = adjoint_strips(*grid, c.ry);
-    int64_t chunks = 2048 / strips;
-    if (chunks < 1) chunks = 1;
-    int64_t zl = (pz + chunks - 1) / chunks;
-    if (zl < 8) zl = 8;
-    if (zl > pz) zl = pz;
-    c.zlen = static_cast<int>(zl);
-    return c;
-}
-
 AdjArgs coeff_grad_args(const pw_grid *grid, const Layout &L, const void *u, const void *v, const void *w,
                         const void *gsu, const void *gsv, const void *gsw) {
     AdjArgs a{};
@@ -627,7 +599,7 @@ AdjArgs coeff_grad_args(const pw_grid *grid, const Layout &L, const void *u, con
 
 pw_status run_coeff_grad(const pw_grid *grid, pw_dtype dtype, const AdjArgs &a, bool grads, double *grad,
                          void *workspace, hipStream_t s) {
-    const TileCfg cfg = coeff_grad_tile(grid, dtype);
+    const TileCfg cfg = coeff_grad_tile(*grid, dtype);
     log_launch(grads ? "pw_advect_adjoint_coeff_grad" : "pw_advect_coeff_grad", grid, dtype, &cfg, "shape rule");
     double *ws = static_cast<double *>(workspace);
     PW_TRY(launch_adjoint_mode(a, dtype, cfg, grads, ws, s));

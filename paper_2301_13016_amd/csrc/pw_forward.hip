@@ -142,8 +142,8 @@ TileCfg default_forward_tile(const FwdArgs &a, pw_dtype dt) {
     // (four wavefronts of two rows, half the rows read twice) where the bytes
     // do.  Measured, tall against short: 512x512x64 (aligned rows) 69.4 / 82.6
     // us, 415x420x169 155 / 177, 1000x300x64 106 / 117, but 96.5 / 98.6 at
-    // 536x186x162 and 43.0 / 36.8 (FP32) at half of 250x250x100's levels; FP64
-    // 250x250x100 63 / 69, 201x143x117 46 / 42.
+    // 536x186x162 and 34.7 / 35.4 at 250x250x100; FP64 250x250x100 63 / 69,
+    // 201x143x117 46 / 42.
     const int64_t pts = a.nx * a.ny * a.nz;
     if (dt == PW_F32) {
         static const ShapeCost small[] = {{1, 2, 1, 1, 0, 64, 2048, 0.90}, {1, 4, 1, 1, 0, 64, 2048, 1.50},

@@ -108,12 +108,16 @@ struct ShapeCost {
 };
 // The cheapest of n shapes, march length included, for a grid of `lead`
 // elements along the lanes, `rows` rows and `march` levels.
-TileCfg cheapest_shape(const ShapeCost *s, int n, int64_t lead, int64_t rows, int64_t march);
+TileCfg cheapest_shape(const ShapeCost *s, int n, int64_t lead, int64_t rows, int64_t march, double start = 1.5);
 
 bool tile_supported(const TileCfg &c, pw_dtype dt);
 bool adjoint_tile_supported(const TileCfg &c);
 TileCfg default_forward_tile(const FwdArgs &a, pw_dtype dt);
 TileCfg default_adjoint_tile(const AdjArgs &a, pw_dtype dt);
+// Launch shape of every coefficient-gradient pass, fixed by the grid's size
+// alone, so that the partials -- and the gradients -- are the same bit for
+// bit whether the wind gradients are computed with them or not.
+TileCfg coeff_grad_tile(const pw_grid &g, pw_dtype dt);
 bool tangent_tile_supported(const TileCfg &c, pw_dtype dt);
 TileCfg default_tangent_tile(const TanArgs &a, pw_dtype dt);
 

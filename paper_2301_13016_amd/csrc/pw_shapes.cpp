@@ -5,10 +5,11 @@
 // every (strip, chunk) is one wavefront.  The chip holds `slots` wavefronts of
 // the shape at once (1024 SIMDs times the one or two that its registers
 // allow), and a wavefront's time is its levels plus the start of its pipeline
-// (three planes before the first level: about one and a half levels).  So with
-// q = wavefronts / slots the march takes
+// (the planes before the first level: `start` levels, 1.5 for three fields and
+// 2.5 for the adjoint's six arrays).  So with q = wavefronts / slots the march
+// takes
 //
-//     cost * rounds(q) * (z + 1.5),
+//     cost * rounds(q) * (z + start),
 //
 // where whole rounds count one each and a partly filled round counts its
 // share, but at least 0.8: below that the wavefronts in flight no longer
@@ -25,14 +26,14 @@
 // "about 2048 wavefronts, chunks of at least 8 levels" that it replaces was
 // 1.5 to 1.65 times slower than the pick: 9.5 -> 3.5 us at 32x32x64 (chunks
 // of one level: a march of eight is latency, and the grid has too few strips
-// to hide it), 130 -> 48 us at 42x587x244 (one column per lane where four
+// to hide it), 130 -> 42 us at 42x587x244 (one column per lane where four
 // leave 5 lanes in 6 idle), 70 -> 43 us at 300x300x75.
 #include "pw_internal.h"
 
 namespace pw {
 
-TileCfg cheapest_shape(const ShapeCost *s, int n, int64_t lead, int64_t rows, int64_t march) {
-    static const int kChunks[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 128};
+TileCfg cheapest_shape(const ShapeCost *s, int n, int64_t lead, int64_t rows, int64_t march, double start) {
+    static const int kChunks[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 16, 24, 32, 48, 64, 128};
     TileCfg best;
     double best_cost = -1.0;
     const int levels = static_cast<int>(march);   // extents are at most 2^30 plus the halo
@@ -45,7 +46,7 @@ TileCfg cheapest_shape(const ShapeCost *s, int n, int64_t lead, int64_t rows, in
             const double q = strips * chunks / s[i].slots;
             const double whole = static_cast<double>(static_cast<int64_t>(q)), part = q - whole;
             const double rounds = whole + (part > 0.0 ? (part > 0.8 ? part : 0.8) : 0.0);
-            const double cost = s[i].cost * rounds * (z + 1.5);
+            const double cost = s[i].cost * rounds * (z + start);
             if (best_cost < 0.0 || cost < best_cost) {
                 best_cost = cost;
                 best = TileCfg{s[i].px, s[i].ry, z, s[i].wpb, s[i].depth, s[i].share};
