@@ -316,18 +316,31 @@ class Coeffs:
         return cls(float(c["tcx"]), float(c["tcy"]), mk(c["tzc1"]), mk(c["tzc2"]), mk(c["tzd1"]), mk(c["tzd2"]))
 
 
+_dtype_codes = {}
+
+
 def _dtype_code(t):
-    import torch
-    m = {torch.float32: PW_F32, torch.float64: PW_F64, torch.bfloat16: PW_BF16, torch.float16: PW_F16}
-    if t.dtype not in m:
+    if not _dtype_codes:
+        import torch
+        _dtype_codes.update({torch.float32: PW_F32, torch.float64: PW_F64, torch.bfloat16: PW_BF16,
+                             torch.float16: PW_F16})
+    code = _dtype_codes.get(t.dtype)
+    if code is None:
         raise TypeError("unsupported input dtype %s" % t.dtype)
-    return m[t.dtype]
+    return code
 
 
 def _stream_handle(stream):
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    """The stream's handle; None is the current device's current stream, read
+    raw where torch has the call for it (its Stream object takes 2.8 us to
+    build, the handle 0.4: a call on a small grid takes about 10 us in all)."""
+    if stream is None:
+        import torch
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None and torch.cuda.is_initialized():
+            return ctypes.c_void_p(raw(torch._C._cuda_getDevice()))
+        stream = torch.cuda.current_stream()
+    return ctypes.c_void_p(stream.cuda_stream)
 
 
 def _grid_from(u, halo):
@@ -336,9 +349,11 @@ def _grid_from(u, halo):
 
 
 def _layout_from(inp, out):
-    if inp.stride(-1) != 1 or out.stride(-1) != 1:
+    isz, isy, isx = inp.stride()
+    osz, osy, osx = out.stride()
+    if isx != 1 or osx != 1:
         raise ValueError("x (last) dimension must be contiguous")
-    return pw_layout(inp.stride(1), inp.stride(0), out.stride(1), out.stride(0))
+    return pw_layout(isy, isz, osy, osz)
 
 
 def _check_inputs(u, v, w):
@@ -355,15 +370,40 @@ def _check_group(ts, what, shape, dtype, device):
     share one set of strides (the library sizes every buffer of a group from
     one layout)."""
     ts = list(ts)
+    strides = []
     for t in ts:
-        if tuple(t.shape) != tuple(shape):
+        if t.shape != shape:
             raise ValueError("%s must have shape %s (got %s)" % (what, tuple(shape), tuple(t.shape)))
         if t.dtype != dtype:
             raise ValueError("%s must be %s (got %s)" % (what, dtype, t.dtype))
         if t.device != device:
             raise ValueError("%s must be on %s (got %s)" % (what, device, t.device))
-    if any(t.stride() != ts[0].stride() for t in ts):
+        strides.append(t.stride())
+    if any(st != strides[0] for st in strides):
         raise ValueError("%s must share one set of strides" % what)
+
+
+def _new_outputs(shape, dtype, device):
+    """Three contiguous tensors (the second and third through empty_like, at
+    half the time of a call with shape, dtype and device)."""
+    import torch
+    a = torch.empty(shape, dtype=dtype, device=device)
+    return a, torch.empty_like(a), torch.empty_like(a)
+
+
+def _cotangents(gsu, gsv, gsw, shape, u):
+    """The cotangents, checked against u's dtype and device, as tensors that
+    share one set of strides with a contiguous last dimension."""
+    gs = (gsu, gsv, gsw)
+    for g in gs:
+        _check_group([g], "cotangents", shape, u.dtype, u.device)
+    strides = [g.stride() for g in gs]
+    if any(st[-1] != 1 for st in strides):
+        gs = [g.contiguous() if st[-1] != 1 else g for g, st in zip(gs, strides)]
+        strides = [g.stride() for g in gs]
+    if not (strides[0] == strides[1] == strides[2]):
+        gs = [g.contiguous() for g in gs]
+    return gs
 
 
 def _compute_dtype(t):
@@ -374,8 +414,7 @@ def _compute_dtype(t):
 def _check_coeffs(coeffs, nz, dtype, device):
     """The vertical arrays: ``dtype`` (float64 for FP64 grids, else float32),
     contiguous, on ``device``, at least nz elements each."""
-    for n in ("tzc1", "tzc2", "tzd1", "tzd2"):
-        t = getattr(coeffs, n)
+    for n, t in (("tzc1", coeffs.tzc1), ("tzc2", coeffs.tzc2), ("tzd1", coeffs.tzd1), ("tzd2", coeffs.tzd2)):
         if t.dtype != dtype:
             raise ValueError("coefficient %s must be %s for this grid (got %s)" % (n, dtype, t.dtype))
         if t.device != device:
@@ -387,20 +426,20 @@ def _check_coeffs(coeffs, nz, dtype, device):
 def advect(u, v, w, coeffs: Coeffs, halo=1, out=None, tile=None, stream=None):
     """su, sv, sw = PW source terms of padded winds u, v, w (torch tensors on the
     GPU; float32, float64, bfloat16 or float16; identical shapes and strides)."""
-    import torch
     _check_inputs(u, v, w)
     grid = _grid_from(u, halo)
     odt = _compute_dtype(u)
     _check_coeffs(coeffs, grid.nz, odt, u.device)
-    if out is None:
-        out = tuple(torch.empty((grid.nz, grid.ny, grid.nx), dtype=odt, device=u.device) for _ in range(3))
-    su, sv, sw = out
-    _check_group(out, "outputs", (grid.nz, grid.ny, grid.nx), odt, u.device)
+    shape = (grid.nz, grid.ny, grid.nx)
+    fresh = out is None
+    su, sv, sw = out = _new_outputs(shape, odt, u.device) if fresh else out
+    if not fresh:
+        _check_group(out, "outputs", shape, odt, u.device)
     layout = _layout_from(u, su)
     c = coeffs.c_struct()
     tl = None if tile is None else pw_tile(*tile)
-    st = pw_advect_ex(grid, layout, _dtype_code(u), u.data_ptr(), v.data_ptr(), w.data_ptr(), c,
-                      su.data_ptr(), sv.data_ptr(), sw.data_ptr(), tl, _stream_handle(stream))
+    st = lib().pw_advect_ex(grid, layout, _dtype_code(u), u.data_ptr(), v.data_ptr(), w.data_ptr(), c,
+                            su.data_ptr(), sv.data_ptr(), sw.data_ptr(), tl, _stream_handle(stream))
     _check(st, "pw_advect")
     return su, sv, sw
 
@@ -410,16 +449,16 @@ def advect_zfast(u, v, w, coeffs: Coeffs, halo=1, out=None, tile=None, stream=No
     (nx+2h, ny+2h, nz+2h) indexed [i, j, k] with k contiguous; the outputs
     (nx, ny, nz) likewise.  Bit-identical to advect() on the transposed
     arrays."""
-    import torch
     _check_inputs(u, v, w)
     pi, pj, pk = u.shape
     grid = pw_grid(pi - 2 * halo, pj - 2 * halo, pk - 2 * halo, halo)
     odt = _compute_dtype(u)
     _check_coeffs(coeffs, grid.nz, odt, u.device)
-    if out is None:
-        out = tuple(torch.empty((grid.nx, grid.ny, grid.nz), dtype=odt, device=u.device) for _ in range(3))
-    su, sv, sw = out
-    _check_group(out, "outputs", (grid.nx, grid.ny, grid.nz), odt, u.device)
+    shape = (grid.nx, grid.ny, grid.nz)
+    fresh = out is None
+    su, sv, sw = out = _new_outputs(shape, odt, u.device) if fresh else out
+    if not fresh:
+        _check_group(out, "outputs", shape, odt, u.device)
     if u.stride(-1) != 1 or su.stride(-1) != 1:
         raise ValueError("z (last) dimension must be contiguous")
     layout = pw_layout_zfast(u.stride(1), u.stride(0), su.stride(1), su.stride(0))
@@ -439,15 +478,15 @@ def advect_bc(u, v, w, coeffs: Coeffs, bc, halo=1, out=None, addends=None, alpha
     followed by advect / advect_epilogue, without touching the halo.  On each
     axis the three fields must all keep, all be periodic or all use
     nearest-cell rules (copy, zero, reflect, reflect_neg)."""
-    import torch
     _check_inputs(u, v, w)
     grid = _grid_from(u, halo)
     odt = _compute_dtype(u)
     _check_coeffs(coeffs, grid.nz, odt, u.device)
-    if out is None:
-        out = tuple(torch.empty((grid.nz, grid.ny, grid.nx), dtype=odt, device=u.device) for _ in range(3))
-    su, sv, sw = out
-    _check_group(out, "outputs", (grid.nz, grid.ny, grid.nx), odt, u.device)
+    shape = (grid.nz, grid.ny, grid.nx)
+    fresh = out is None
+    su, sv, sw = out = _new_outputs(shape, odt, u.device) if fresh else out
+    if not fresh:
+        _check_group(out, "outputs", shape, odt, u.device)
     layout = _layout_from(u, su)
     modes = (pw_halo_modes * 3)(*(pw_halo_modes(*(_halo_code(m) for m in t)) for t in _per_field_modes(bc, 3)))
     ep = None
@@ -466,7 +505,6 @@ def advect_zfast_epilogue(u, v, w, coeffs: Coeffs, addends, alpha=1.0, halo=1, o
     advect_zfast); ``addends`` are (nx, ny, nz)-indexed tensors in the output
     dtype, each either its output (accumulation in place) or disjoint from
     the outputs."""
-    import torch
     _check_inputs(u, v, w)
     pi, pj, pk = u.shape
     grid = pw_grid(pi - 2 * halo, pj - 2 * halo, pk - 2 * halo, halo)
@@ -474,10 +512,11 @@ def advect_zfast_epilogue(u, v, w, coeffs: Coeffs, addends, alpha=1.0, halo=1, o
     _check_coeffs(coeffs, grid.nz, odt, u.device)
     cu, cv, cw = addends
     _check_group(addends, "addends", (grid.nx, grid.ny, grid.nz), odt, u.device)
-    if out is None:
-        out = tuple(torch.empty((grid.nx, grid.ny, grid.nz), dtype=odt, device=u.device) for _ in range(3))
-    su, sv, sw = out
-    _check_group(out, "outputs", (grid.nx, grid.ny, grid.nz), odt, u.device)
+    shape = (grid.nx, grid.ny, grid.nz)
+    fresh = out is None
+    su, sv, sw = out = _new_outputs(shape, odt, u.device) if fresh else out
+    if not fresh:
+        _check_group(out, "outputs", shape, odt, u.device)
     if u.stride(-1) != 1 or su.stride(-1) != 1:
         raise ValueError("z (last) dimension must be contiguous")
     if su.stride() != cu.stride():
@@ -524,22 +563,18 @@ def advect_adjoint(u, v, w, coeffs: Coeffs, gsu, gsv, gsw, halo=1, out=None, til
     _check_inputs(u, v, w)
     grid = _grid_from(u, halo)
     _check_coeffs(coeffs, grid.nz, _compute_dtype(u), u.device)
-    if out is None:
-        out = tuple(torch.empty_like(u) for _ in range(3))
-    gu, gv, gw = out
-    for g in (gsu, gsv, gsw):
-        _check_group([g], "cotangents", (grid.nz, grid.ny, grid.nx), u.dtype, u.device)
-    gsu, gsv, gsw = (g.contiguous() if g.stride(-1) != 1 else g for g in (gsu, gsv, gsw))
-    if not (gsu.stride() == gsv.stride() == gsw.stride()):
-        gsu, gsv, gsw = (g.contiguous() for g in (gsu, gsv, gsw))
+    fresh = out is None
+    gu, gv, gw = out = (torch.empty_like(u), torch.empty_like(u), torch.empty_like(u)) if fresh else out
+    gsu, gsv, gsw = _cotangents(gsu, gsv, gsw, (grid.nz, grid.ny, grid.nx), u)
     layout = _layout_from(u, gsu)
-    _check_group(out, "gradients", tuple(u.shape), u.dtype, u.device)
+    if not fresh:
+        _check_group(out, "gradients", tuple(u.shape), u.dtype, u.device)
     if gu.stride() != u.stride():
         raise ValueError("gradients must share the inputs' strides")
     tl = None if tile is None else pw_tile(*tile)
-    st = pw_advect_adjoint_ex(grid, layout, _dtype_code(u), u.data_ptr(), v.data_ptr(), w.data_ptr(),
-                              coeffs.c_struct(), gsu.data_ptr(), gsv.data_ptr(), gsw.data_ptr(),
-                              gu.data_ptr(), gv.data_ptr(), gw.data_ptr(), tl, _stream_handle(stream))
+    st = lib().pw_advect_adjoint_ex(grid, layout, _dtype_code(u), u.data_ptr(), v.data_ptr(), w.data_ptr(),
+                                    coeffs.c_struct(), gsu.data_ptr(), gsv.data_ptr(), gsw.data_ptr(),
+                                    gu.data_ptr(), gv.data_ptr(), gw.data_ptr(), tl, _stream_handle(stream))
     _check(st, "pw_advect_adjoint")
     return gu, gv, gw
 
@@ -547,7 +582,6 @@ def advect_adjoint(u, v, w, coeffs: Coeffs, gsu, gsv, gsw, halo=1, out=None, til
 def advect_tangent(u, v, w, coeffs: Coeffs, du, dv, dw, halo=1, out=None, tile=None, stream=None):
     """tu, tv, tw = J(u, v, w) (du, dv, dw), interior-shaped; du, dv, dw are
     padded like u (the halo is read)."""
-    import torch
     _check_inputs(u, v, w)
     grid = _grid_from(u, halo)
     _check_coeffs(coeffs, grid.nz, _compute_dtype(u), u.device)
@@ -558,16 +592,16 @@ def advect_tangent(u, v, w, coeffs: Coeffs, du, dv, dw, halo=1, out=None, tile=N
         du, dv, dw = (d.contiguous() for d in (du, dv, dw))
         if du.stride() != u.stride():
             raise ValueError("the direction must share the inputs' strides")
-    if out is None:
-        nz, ny, nx = (s - 2 * halo for s in u.shape)
-        out = tuple(torch.empty((nz, ny, nx), dtype=u.dtype, device=u.device) for _ in range(3))
-    tu, tv, tw = out
-    _check_group(out, "outputs", (grid.nz, grid.ny, grid.nx), u.dtype, u.device)
+    shape = (grid.nz, grid.ny, grid.nx)
+    fresh = out is None
+    tu, tv, tw = out = _new_outputs(shape, u.dtype, u.device) if fresh else out
+    if not fresh:
+        _check_group(out, "outputs", shape, u.dtype, u.device)
     layout = _layout_from(u, tu)
     tl = None if tile is None else pw_tile(*tile)
-    st = pw_advect_tangent_ex(grid, layout, _dtype_code(u), u.data_ptr(), v.data_ptr(), w.data_ptr(),
-                              coeffs.c_struct(), du.data_ptr(), dv.data_ptr(), dw.data_ptr(),
-                              tu.data_ptr(), tv.data_ptr(), tw.data_ptr(), tl, _stream_handle(stream))
+    st = lib().pw_advect_tangent_ex(grid, layout, _dtype_code(u), u.data_ptr(), v.data_ptr(), w.data_ptr(),
+                                    coeffs.c_struct(), du.data_ptr(), dv.data_ptr(), dw.data_ptr(),
+                                    tu.data_ptr(), tv.data_ptr(), tw.data_ptr(), tl, _stream_handle(stream))
     _check(st, "pw_advect_tangent")
     return tu, tv, tw
 
@@ -590,11 +624,7 @@ def advect_coeff_grad(u, v, w, gsu, gsv, gsw, halo=1, stream=None, out=None, sta
     import torch
     _check_inputs(u, v, w)
     grid = _grid_from(u, halo)
-    for g in (gsu, gsv, gsw):
-        _check_group([g], "cotangents", (grid.nz, grid.ny, grid.nx), u.dtype, u.device)
-    gs = [g.contiguous() if g.stride(-1) != 1 else g for g in (gsu, gsv, gsw)]
-    if not (gs[0].stride() == gs[1].stride() == gs[2].stride()):
-        gs = [g.contiguous() for g in gs]
+    gs = _cotangents(gsu, gsv, gsw, (grid.nz, grid.ny, grid.nx), u)
     layout = _layout_from(u, gs[0])
     nz = int(grid.nz)
     if out is None:
@@ -632,16 +662,12 @@ def advect_adjoint_coeff_grad(u, v, w, coeffs: Coeffs, gsu, gsv, gsw, halo=1, ou
     _check_inputs(u, v, w)
     grid = _grid_from(u, halo)
     _check_coeffs(coeffs, grid.nz, _compute_dtype(u), u.device)
-    if out is None:
-        out = tuple(torch.empty_like(u) for _ in range(3))
-    gu, gv, gw = out
-    for g in (gsu, gsv, gsw):
-        _check_group([g], "cotangents", (grid.nz, grid.ny, grid.nx), u.dtype, u.device)
-    gsu, gsv, gsw = (g.contiguous() if g.stride(-1) != 1 else g for g in (gsu, gsv, gsw))
-    if not (gsu.stride() == gsv.stride() == gsw.stride()):
-        gsu, gsv, gsw = (g.contiguous() for g in (gsu, gsv, gsw))
+    fresh = out is None
+    gu, gv, gw = out = (torch.empty_like(u), torch.empty_like(u), torch.empty_like(u)) if fresh else out
+    gsu, gsv, gsw = _cotangents(gsu, gsv, gsw, (grid.nz, grid.ny, grid.nx), u)
     layout = _layout_from(u, gsu)
-    _check_group(out, "gradients", tuple(u.shape), u.dtype, u.device)
+    if not fresh:
+        _check_group(out, "gradients", tuple(u.shape), u.dtype, u.device)
     if gu.stride() != u.stride():
         raise ValueError("gradients must share the inputs' strides")
     nz = int(grid.nz)
@@ -649,11 +675,11 @@ def advect_adjoint_coeff_grad(u, v, w, coeffs: Coeffs, gsu, gsv, gsw, halo=1, ou
         grad_out = torch.empty(6 * nz + 2, dtype=torch.float64, device=u.device)
     _check_group([grad_out], "grad_out", (6 * nz + 2,), torch.float64, u.device)
     need = ctypes.c_int64()
-    _check(lib().pw_advect_coeff_grad_workspace(ctypes.byref(grid), _dtype_code(u), ctypes.byref(need)),
-           "pw_advect_coeff_grad_workspace")
+    code = _dtype_code(u)
+    _check(lib().pw_advect_coeff_grad_workspace(grid, code, need), "pw_advect_coeff_grad_workspace")
     ws = torch.empty(max(1, need.value // 8), dtype=torch.float64, device=u.device)
-    st = lib().pw_advect_adjoint_coeff_grad(ctypes.byref(grid), ctypes.byref(layout), _dtype_code(u), u.data_ptr(),
-                                            v.data_ptr(), w.data_ptr(), ctypes.byref(coeffs.c_struct()),
+    st = lib().pw_advect_adjoint_coeff_grad(grid, layout, code, u.data_ptr(), v.data_ptr(), w.data_ptr(),
+                                            coeffs.c_struct(),
                                             gsu.data_ptr(), gsv.data_ptr(), gsw.data_ptr(), gu.data_ptr(),
                                             gv.data_ptr(), gw.data_ptr(), grad_out.data_ptr(), ws.data_ptr(),
                                             need.value, _stream_handle(stream))
