@@ -488,8 +488,8 @@ pw_status pw_halo_fill(const pw_grid *grid, const pw_layout *layout, pw_dtype dt
  * (ZERO: only set to zero; KEEP: the axis is left alone).  On one GPU this
  * is the reverse of the halo exchange: halo gradients go back to their
  * owners.  PW_F32 / PW_F64 only (PW_ERR_UNSUPPORTED otherwise); other
- * arguments and errors as pw_halo_fill.  Three small launches on
- * hip_stream. */
+ * arguments and errors as pw_halo_fill.  One small launch on hip_stream
+ * (halos wider than one layer: up to three). */
 pw_status pw_halo_fold(const pw_grid *grid, const pw_layout *layout, pw_dtype dtype, void *const fields[],
                        const pw_halo_modes modes[], int32_t nfields, void *hip_stream);
 
@@ -517,6 +517,19 @@ pw_status pw_halo_fold(const pw_grid *grid, const pw_layout *layout, pw_dtype dt
 pw_status pw_advect_bc(const pw_grid *grid, const pw_layout *layout, pw_dtype in_dtype, const void *u,
                        const void *v, const void *w, const pw_coeffs *coeffs, const pw_halo_modes bc[3],
                        const pw_epilogue *ep, void *su, void *sv, void *sw, const pw_tile *tile, void *hip_stream);
+
+/* The adjoint of pw_advect_bc (without an epilogue): the gradients of
+ * <su, gsu> + <sv, gsv> + <sw, gsw> with respect to u, v, w as given, before
+ * the boundary rules.  Bit for bit pw_halo_fill of copies of u, v, w with the
+ * rules bc, pw_advect_adjoint_ex on them and pw_halo_fold of the gradients,
+ * but the values are read through the rules and nothing is copied: two
+ * launches on hip_stream (the fold of halos wider than one layer takes up to
+ * three).  Rules and their errors as pw_advect_bc; dtypes, layout, tiles,
+ * ownership and other errors as pw_advect_adjoint_ex. */
+pw_status pw_advect_bc_adjoint(const pw_grid *grid, const pw_layout *layout, pw_dtype dtype,
+                               const void *u, const void *v, const void *w, const pw_coeffs *coeffs,
+                               const pw_halo_modes bc[3], const void *gsu, const void *gsv, const void *gsw,
+                               void *gu, void *gv, void *gw, const pw_tile *tile, void *hip_stream);
 
 /* Library version string (static storage). */
 const char *pw_version(void);

@@ -125,6 +125,9 @@ _SIGNATURES = {
     "pw_advect_bc": [ctypes.POINTER(pw_grid), ctypes.POINTER(pw_layout), ctypes.c_int, _P, _P, _P,
                      ctypes.POINTER(pw_coeffs), ctypes.POINTER(pw_halo_modes), ctypes.POINTER(pw_epilogue),
                      _P, _P, _P, ctypes.POINTER(pw_tile), _P],
+    "pw_advect_bc_adjoint": [ctypes.POINTER(pw_grid), ctypes.POINTER(pw_layout), ctypes.c_int, _P, _P, _P,
+                             ctypes.POINTER(pw_coeffs), ctypes.POINTER(pw_halo_modes), _P, _P, _P, _P, _P, _P,
+                             ctypes.POINTER(pw_tile), _P],
     "pw_halo_fill": [ctypes.POINTER(pw_grid), ctypes.POINTER(pw_layout), ctypes.c_int, ctypes.POINTER(_P),
                      ctypes.POINTER(pw_halo_modes), ctypes.c_int32, _P],
     "pw_halo_fold": [ctypes.POINTER(pw_grid), ctypes.POINTER(pw_layout), ctypes.c_int, ctypes.POINTER(_P),
@@ -816,11 +819,45 @@ def halo_fold(fields, modes, halo=1, stream=None):
     return _halo_call(pw_halo_fold, "pw_halo_fold", fields, modes, halo, stream)
 
 
+def _bc_adjoint_reads_through(u, v, w, codes):
+    """Whether pw_advect_bc_adjoint takes this call: contiguous winds of one
+    shape (gradients then share their strides) in a dtype the adjoint has, and
+    on each axis rules of one kind (keep, periodic, nearest cell) for the
+    three fields, so that they share the remapping of reads.  Everything else
+    goes through filled copies."""
+    import torch
+    keep, periodic = HALO_MODES["keep"], HALO_MODES["periodic"]
+    kind = lambda m: m if m in (keep, periodic) else -1  # noqa: E731
+    return (u.dim() == 3 and u.shape == v.shape == w.shape and u.dtype == v.dtype == w.dtype
+            and u.device == v.device == w.device and u.dtype in (torch.float32, torch.float64)
+            and u.is_contiguous() and v.is_contiguous() and w.is_contiguous()
+            and all(m in HALO_MODES.values() for t in codes for m in t)
+            and all(kind(a) == kind(b) == kind(c) for a, b, c in zip(*codes)))
+
+
+def _bc_adjoint_through(u, v, w, coeffs, codes, gsu, gsv, gsw, halo, stream):
+    import torch
+    grid = _grid_from(u, halo)
+    _check_coeffs(coeffs, grid.nz, _compute_dtype(u), u.device)
+    gu, gv, gw = torch.empty_like(u), torch.empty_like(u), torch.empty_like(u)
+    gsu, gsv, gsw = _cotangents(gsu, gsv, gsw, (grid.nz, grid.ny, grid.nx), u)
+    modes = (pw_halo_modes * 3)(*(pw_halo_modes(*t) for t in codes))
+    st = lib().pw_advect_bc_adjoint(grid, _layout_from(u, gsu), _dtype_code(u), u.data_ptr(), v.data_ptr(),
+                                    w.data_ptr(), coeffs.c_struct(), modes, gsu.data_ptr(), gsv.data_ptr(),
+                                    gsw.data_ptr(), gu.data_ptr(), gv.data_ptr(), gw.data_ptr(), None,
+                                    _stream_handle(stream))
+    _check(st, "pw_advect_bc_adjoint")
+    return gu, gv, gw
+
+
 def advect_bc_adjoint(u, v, w, coeffs: Coeffs, bc, gsu, gsv, gsw, halo=1, stream=None):
     """Gradients of <advect_bc(u, v, w, bc), (gsu, gsv, gsw)> with respect to
     the padded u, v, w as given (before the boundary rules): the adjoint
     kernel at the filled state, then the fold.  Halo entries on axes whose
     rule is not keep come out zero."""
+    codes = [tuple(_halo_code(m) for m in t) for t in _per_field_modes(bc, 3)]
+    if _bc_adjoint_reads_through(u, v, w, codes):
+        return _bc_adjoint_through(u, v, w, coeffs, codes, gsu, gsv, gsw, halo, stream)
     filled = [x.clone() for x in (u, v, w)]
     halo_fill(filled, bc, halo=halo, stream=stream)
     grads = advect_adjoint(*filled, coeffs, gsu, gsv, gsw, halo=halo, stream=stream)

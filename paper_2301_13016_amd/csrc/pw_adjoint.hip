@@ -43,6 +43,7 @@
 // z-chunk fastest 82.6 us, x fastest 77.4; six z-chunks 96.8 and 85.1.  The
 // carried terms count where arithmetic is added to the same accesses: wind and
 // coefficient gradients in one pass over 512x512x64 226 us before, 208 now.
+#include "pw_bc.h"
 #include "pw_internal.h"
 #include "pw_lanes.h"
 #include "pw_reduce.h"
@@ -69,11 +70,15 @@ template <typename T> struct AdjK {
     int32_t ntx, nty, nzc, zlen, wpb;
     // coefficient partials (modes with kModeCg): ws[q][level][strip], strip = ty * ntx + tx
     double *ws;
+    // boundary rules by addressing (modes with kModeBc), see FwdArgs
+    int32_t bcx, bcy, bcz;
+    uint32_t bcv;
 };
 
 // What a launch computes: the gradients of u, v, w (kModeGrad), the
-// per-strip coefficient partials (kModeCg; see cg_level), or both in one pass.
-constexpr int kModeGrad = 1, kModeCg = 2;
+// per-strip coefficient partials (kModeCg; see cg_level), or both in one pass;
+// with kModeBc the values of halo cells are read through the boundary rules.
+constexpr int kModeGrad = 1, kModeCg = 2, kModeBc = 4;
 
 // One padded z-plane of the strip: rows 0..RY+1 are padded rows jb-1 .. jb+RY.
 template <typename T, int RY> struct APlane {
@@ -81,6 +86,7 @@ template <typename T, int RY> struct APlane {
     T ru[RY + 2], rv[RY + 2], rw[RY + 2];
     bool zok;   // the plane is an interior level, so its cotangents exist (wave-uniform)
     int kcls;   // position class of the plane (wave-uniform), see pos_class
+    uint32_t zcode;   // kModeBc: value codes of the plane's z rule (wave-uniform)
 };
 
 // Bits of StripAddr::mask for one loaded row and the lane's column: bit
@@ -93,6 +99,8 @@ template <typename T, int RY> struct StripAddr {
     uint32_t voff[RY + 2];   // byte offsets of the value rows (kOutside: never read)
     uint32_t roff[RY + 2];   // byte offsets of the cotangent rows (kOutside: none there)
     uint32_t mask[RY + 2];   // per row, see kCotOk
+    uint32_t code[RY + 2];   // kModeBc: value codes of the x and y rules, see bc_compose3
+    int coded;               // kModeBc: any of them is set (wave-uniform)
     int corner;              // the strip reaches the x and the y halo (wave-uniform)
 };
 
@@ -145,14 +153,18 @@ template <typename T> __device__ __forceinline__ void bstore(T x, __amdgpu_buffe
     }
 }
 
-template <typename T, int RY>
+template <typename T, int RY, int Mode>
 __device__ __forceinline__ void load_aplane(APlane<T, RY> &P, const AdjK<T> &a, int kp, const StripAddr<T, RY> &s) {
     const int pz = a.nz + 2 * a.h;
     const bool in = kp >= 0 && kp < pz;
     // (readfirstlane: what depends on the class must stay scalar, or every
     // load loops over the lanes' descriptors)
     P.kcls = __builtin_amdgcn_readfirstlane(pos_class(kp, a.h, a.nz));
-    const int kv = min(max(kp, 0), pz - 1);
+    int kv = min(max(kp, 0), pz - 1);
+    if constexpr (Mode & kModeBc) {
+        kv = bc_src(kv, a.nz, a.h, a.bcz);
+        P.zcode = P.kcls ? (a.bcv >> 16) & 0x3Fu : 0u;
+    }
     const int64_t pb = static_cast<int64_t>(kv) * a.in_sz * static_cast<int64_t>(sizeof(T));
     const int64_t vbytes = in ? a.in_sz * static_cast<int64_t>(sizeof(T)) : 0;
     const auto bu = plane_rsrc(reinterpret_cast<const char *>(a.u) + pb, vbytes);
@@ -174,6 +186,17 @@ __device__ __forceinline__ void load_aplane(APlane<T, RY> &P, const AdjK<T> &a, 
             ow[r] |= (unread >> 2) << 31;
         }
     }
+    if constexpr (Mode & kModeBc) {
+        if ((static_cast<uint32_t>(s.coded) | P.zcode) != 0) {   // cells whose rule is zero
+#pragma unroll
+            for (int r = 0; r < RY + 2; ++r) {
+                const uint32_t c = bc_compose3(s.code[r], P.zcode);
+                ou[r] |= (c & 0x02u) << 30;
+                ov[r] |= (c & 0x08u) << 28;
+                ow[r] |= (c & 0x20u) << 26;
+            }
+        }
+    }
 #pragma unroll
     for (int r = 0; r < RY + 2; ++r) {
         P.u[r] = bload<T>(bu, ou[r]);
@@ -193,6 +216,20 @@ __device__ __forceinline__ void load_aplane(APlane<T, RY> &P, const AdjK<T> &a, 
         P.ru[r] = bload<T>(cu, s.roff[r]);
         P.rv[r] = bload<T>(cv, s.roff[r]);
         P.rw[r] = bload<T>(cw, s.roff[r]);
+    }
+}
+
+// Negate the values whose boundary rules do, once per plane at its first use
+// (cells that are not read keep their 0).
+template <typename T, int RY>
+__device__ __forceinline__ void negate_aplane(APlane<T, RY> &P, const StripAddr<T, RY> &s) {
+    if (((static_cast<uint32_t>(s.coded) | P.zcode) & 0x15u) == 0) return;
+#pragma unroll
+    for (int r = 0; r < RY + 2; ++r) {
+        const uint32_t c = bc_compose3(s.code[r], P.zcode), rd = s.mask[r] >> (3 * P.kcls);
+        P.u[r] = (c & 0x01u) && (rd & 1u) ? -P.u[r] : P.u[r];
+        P.v[r] = (c & 0x04u) && (rd & 2u) ? -P.v[r] : P.v[r];
+        P.w[r] = (c & 0x10u) && (rd & 4u) ? -P.w[r] : P.w[r];
     }
 }
 
@@ -430,9 +467,15 @@ __global__ __launch_bounds__(MaxT) void pw_adjoint_kernel(AdjK<T> a) {
         const int prow = jb - 1 + r;
         const int ir = prow - a.h;
         const int jcls = (prow < 0 || prow >= py) ? 3 : pos_class(prow, a.h, a.ny);
+        int vrow = prow, vcol = pcol;   // where the value is read
+        if constexpr (Mode & kModeBc) {
+            vrow = bc_src(prow, a.ny, a.h, a.bcy);
+            vcol = bc_src(pcol, a.nx, a.h, a.bcx);
+            s.code[r] = bc_compose3(icls ? a.bcv & 0x3Fu : 0u, jcls ? (a.bcv >> 8) & 0x3Fu : 0u);
+        }
         s.voff[r] = (jcls == 3 || icls == 3)
                         ? kOutside
-                        : static_cast<uint32_t>((prow * a.in_sy + pcol) * static_cast<int>(sizeof(T)));
+                        : static_cast<uint32_t>((vrow * a.in_sy + vcol) * static_cast<int>(sizeof(T)));
         yhalo = yhalo || jcls != 0;
         uint32_t m = (rcol && ir >= 0 && ir < a.ny) ? kCotOk : 0u;
 #pragma unroll
@@ -447,6 +490,9 @@ __global__ __launch_bounds__(MaxT) void pw_adjoint_kernel(AdjK<T> a) {
         s.roff[r] = (m & kCotOk) ? static_cast<uint32_t>((ir * a.out_sy + icol) * static_cast<int>(sizeof(T))) : kOutside;
     }
     const bool xhalo = __ballot(icls != 0) != 0;
+    if constexpr (Mode & kModeBc)   // the codes that some row and lane of the strip has
+        s.coded = __builtin_amdgcn_readfirstlane(static_cast<int>((xhalo ? a.bcv & 0x3Fu : 0u) |
+                                                                  (yhalo ? (a.bcv >> 8) & 0x3Fu : 0u)));
     s.corner = __builtin_amdgcn_readfirstlane(xhalo && yhalo ? 1 : 0);
     uint32_t goff[RY];
 #pragma unroll
@@ -464,6 +510,7 @@ __global__ __launch_bounds__(MaxT) void pw_adjoint_kernel(AdjK<T> a) {
     // drains the prefetch.
 #define PW_ALEVEL(C, P)                                                                                \
     do {                                                                                               \
+        if constexpr (Mode & kModeBc) negate_aplane<T, RY>(P, s);   /* first use of plane k+1 */       \
         Carry<T, RY> n;                                                                                \
         carry_of<T, RY>(n, C, a, k);                                                                   \
         if constexpr (Mode & kModeGrad) adj_level<T, RY>(m, n, C, P, a, k, goff);                      \
@@ -475,18 +522,22 @@ __global__ __launch_bounds__(MaxT) void pw_adjoint_kernel(AdjK<T> a) {
     if constexpr (Depth == 1) {
         // three-plane ring: planes k, k+1 feed level k, k+2 in flight
         APlane<T, RY> A, B, C;
-        load_aplane<T, RY>(C, a, k0 - 1, s);
-        load_aplane<T, RY>(A, a, k0, s);
-        load_aplane<T, RY>(B, a, k0 + 1, s);
+        load_aplane<T, RY, Mode>(C, a, k0 - 1, s);
+        load_aplane<T, RY, Mode>(A, a, k0, s);
+        load_aplane<T, RY, Mode>(B, a, k0 + 1, s);
+        if constexpr (Mode & kModeBc) {
+            negate_aplane<T, RY>(C, s);
+            negate_aplane<T, RY>(A, s);
+        }
         carry_of<T, RY>(m, C, a, k0 - 1);
         for (;;) {
-            load_aplane<T, RY>(C, a, min(k + 2, k1), s);
+            load_aplane<T, RY, Mode>(C, a, min(k + 2, k1), s);
             PW_ALEVEL(A, B);
             if (++k >= k1) break;
-            load_aplane<T, RY>(A, a, min(k + 2, k1), s);
+            load_aplane<T, RY, Mode>(A, a, min(k + 2, k1), s);
             PW_ALEVEL(B, C);
             if (++k >= k1) break;
-            load_aplane<T, RY>(B, a, min(k + 2, k1), s);
+            load_aplane<T, RY, Mode>(B, a, min(k + 2, k1), s);
             PW_ALEVEL(C, A);
             if (++k >= k1) break;
         }
@@ -494,22 +545,26 @@ __global__ __launch_bounds__(MaxT) void pw_adjoint_kernel(AdjK<T> a) {
         // four-plane ring: planes k+2 and k+3 in flight
         static_assert(Depth == 2, "prefetch depth 1 or 2");
         APlane<T, RY> A, B, C, D;
-        load_aplane<T, RY>(D, a, k0 - 1, s);
-        load_aplane<T, RY>(A, a, k0, s);
-        load_aplane<T, RY>(B, a, k0 + 1, s);
-        load_aplane<T, RY>(C, a, min(k0 + 2, k1), s);
+        load_aplane<T, RY, Mode>(D, a, k0 - 1, s);
+        load_aplane<T, RY, Mode>(A, a, k0, s);
+        load_aplane<T, RY, Mode>(B, a, k0 + 1, s);
+        load_aplane<T, RY, Mode>(C, a, min(k0 + 2, k1), s);
+        if constexpr (Mode & kModeBc) {
+            negate_aplane<T, RY>(D, s);
+            negate_aplane<T, RY>(A, s);
+        }
         carry_of<T, RY>(m, D, a, k0 - 1);
         for (;;) {
-            load_aplane<T, RY>(D, a, min(k + 3, k1), s);
+            load_aplane<T, RY, Mode>(D, a, min(k + 3, k1), s);
             PW_ALEVEL(A, B);
             if (++k >= k1) break;
-            load_aplane<T, RY>(A, a, min(k + 3, k1), s);
+            load_aplane<T, RY, Mode>(A, a, min(k + 3, k1), s);
             PW_ALEVEL(B, C);
             if (++k >= k1) break;
-            load_aplane<T, RY>(B, a, min(k + 3, k1), s);
+            load_aplane<T, RY, Mode>(B, a, min(k + 3, k1), s);
             PW_ALEVEL(C, D);
             if (++k >= k1) break;
-            load_aplane<T, RY>(C, a, min(k + 3, k1), s);
+            load_aplane<T, RY, Mode>(C, a, min(k + 3, k1), s);
             PW_ALEVEL(D, A);
             if (++k >= k1) break;
         }
@@ -540,6 +595,10 @@ pw_status launch_adj_t(const AdjArgs &g, const TileCfg &cfg, double *ws, hipStre
     a.ny = static_cast<int32_t>(g.ny);
     a.nz = static_cast<int32_t>(g.nz);
     a.h = g.h;
+    a.bcx = g.bcx;
+    a.bcy = g.bcy;
+    a.bcz = g.bcz;
+    a.bcv = g.bcv;
     a.in_sz = g.in_sz;
     a.out_sz = g.out_sz;
     a.in_sy = static_cast<int32_t>(g.in_sy);
@@ -591,6 +650,7 @@ pw_status launch_adj_mode(const AdjArgs &g, const TileCfg &cfg, int mode, double
         case kModeGrad: return launch_adj_dt<T, kModeGrad>(g, c, ws, s);
         case kModeCg: return launch_adj_dt<T, kModeCg>(g, c, ws, s);
         case kModeGrad | kModeCg: return launch_adj_dt<T, kModeGrad | kModeCg>(g, c, ws, s);
+        case kModeGrad | kModeBc: return launch_adj_dt<T, kModeGrad | kModeBc>(g, c, ws, s);
     }
     return fail(PW_ERR_INVALID_ARG, "adjoint mode %d", mode);
 }
@@ -646,6 +706,15 @@ pw_status launch_adjoint_mode(const AdjArgs &a, pw_dtype dt, const TileCfg &cfg,
 
 pw_status launch_adjoint(const AdjArgs &a, pw_dtype dt, const TileCfg &cfg, hipStream_t s) {
     return launch_adjoint_mode(a, dt, cfg, true, nullptr, s);
+}
+
+pw_status launch_adjoint_bc(const AdjArgs &a, pw_dtype dt, const TileCfg &cfg, hipStream_t s) {
+    if (!adjoint_tile_supported(cfg)) return fail(PW_ERR_INVALID_ARG, "unsupported adjoint tile configuration");
+    switch (dt) {
+        case PW_F32: return launch_adj_mode<float>(a, cfg, kModeGrad | kModeBc, nullptr, s);
+        case PW_F64: return launch_adj_mode<double>(a, cfg, kModeGrad | kModeBc, nullptr, s);
+        default: return fail(PW_ERR_UNSUPPORTED, "adjoint dtype %d", static_cast<int>(dt));
+    }
 }
 
 }  // namespace pw

@@ -325,6 +325,38 @@ pw_status forward_shape(const pw_grid *grid, const FwdArgs &a, pw_dtype dt, cons
     return PW_OK;
 }
 
+// bc[f] = rules of field f (u, v, w).  A depth-one read of a halo cell
+// goes to its periodic source or to the nearest interior cell (which
+// is also the mirror image of the cells next to the face); ZERO and
+// REFLECT_NEG then change the value.  The remapping is shared by the
+// three fields, so per axis they must agree on it.
+pw_status boundary_rules(const pw_grid *grid, const pw_halo_modes bc[3], int32_t (&addr)[3], uint32_t *bcv) {
+    const int64_t n[3] = {grid->nx, grid->ny, grid->nz};
+    for (int32_t &x : addr) x = -1;
+    *bcv = 0;
+    for (int f = 0; f < 3; ++f) {
+        const int32_t m[3] = {bc[f].x, bc[f].y, bc[f].z};
+        for (int d = 0; d < 3; ++d) {
+            if (m[d] < PW_HALO_KEEP || m[d] > PW_HALO_REFLECT_NEG)
+                return fail(PW_ERR_INVALID_ARG, "unknown boundary rule %d (field %c, axis %c)", m[d], "uvw"[f],
+                            "xyz"[d]);
+            if ((m[d] == PW_HALO_REFLECT || m[d] == PW_HALO_REFLECT_NEG) && n[d] < grid->halo)
+                return fail(PW_ERR_INVALID_ARG, "reflect on axis %c needs at least %d interior cells",
+                            "xyz"[d], grid->halo);
+            const int32_t cls = m[d] == PW_HALO_KEEP ? PW_HALO_KEEP
+                                : m[d] == PW_HALO_PERIODIC ? PW_HALO_PERIODIC : PW_HALO_COPY;
+            if (addr[d] >= 0 && addr[d] != cls)
+                return fail(PW_ERR_UNSUPPORTED,
+                            "axis %c: u, v and w must all keep, all be periodic, or all use nearest-cell rules "
+                            "(copy, zero, reflect, reflect_neg)", "xyz"[d]);
+            addr[d] = cls;
+            const uint32_t code = m[d] == PW_HALO_REFLECT_NEG ? 1u : (m[d] == PW_HALO_ZERO ? 2u : 0u);
+            *bcv |= code << (8 * d + 2 * f);
+        }
+    }
+    return PW_OK;
+}
+
 // Forward with optional boundary rules (bc, NULL: read the stored halo) and
 // optional fused epilogue (ep, NULL: out = F): validation and launch.
 pw_status advect_general(const pw_grid *grid, const pw_layout *layout, pw_dtype in_dtype, const void *u,
@@ -342,38 +374,11 @@ pw_status advect_general(const pw_grid *grid, const pw_layout *layout, pw_dtype 
     const char *how = "given";
     PW_TRY(forward_shape(grid, a, in_dtype, tile, &cfg, &how));
     if (bc) {
-        // bc[f] = rules of field f (u, v, w).  A depth-one read of a halo cell
-        // goes to its periodic source or to the nearest interior cell (which
-        // is also the mirror image of the cells next to the face); ZERO and
-        // REFLECT_NEG then change the value.  The remapping is shared by the
-        // three fields, so per axis they must agree on it.
-        const int64_t n[3] = {grid->nx, grid->ny, grid->nz};
-        int32_t addr[3] = {-1, -1, -1};
-        uint32_t bcv = 0;
-        for (int f = 0; f < 3; ++f) {
-            const int32_t m[3] = {bc[f].x, bc[f].y, bc[f].z};
-            for (int d = 0; d < 3; ++d) {
-                if (m[d] < PW_HALO_KEEP || m[d] > PW_HALO_REFLECT_NEG)
-                    return fail(PW_ERR_INVALID_ARG, "unknown boundary rule %d (field %c, axis %c)", m[d], "uvw"[f],
-                                "xyz"[d]);
-                if ((m[d] == PW_HALO_REFLECT || m[d] == PW_HALO_REFLECT_NEG) && n[d] < grid->halo)
-                    return fail(PW_ERR_INVALID_ARG, "reflect on axis %c needs at least %d interior cells",
-                                "xyz"[d], grid->halo);
-                const int32_t cls = m[d] == PW_HALO_KEEP ? PW_HALO_KEEP
-                                    : m[d] == PW_HALO_PERIODIC ? PW_HALO_PERIODIC : PW_HALO_COPY;
-                if (addr[d] >= 0 && addr[d] != cls)
-                    return fail(PW_ERR_UNSUPPORTED,
-                                "axis %c: u, v and w must all keep, all be periodic, or all use nearest-cell rules "
-                                "(copy, zero, reflect, reflect_neg)", "xyz"[d]);
-                addr[d] = cls;
-                const uint32_t code = m[d] == PW_HALO_REFLECT_NEG ? 1u : (m[d] == PW_HALO_ZERO ? 2u : 0u);
-                bcv |= code << (8 * d + 2 * f);
-            }
-        }
+        int32_t addr[3];
+        PW_TRY(boundary_rules(grid, bc, addr, &a.bcv));
         a.bcx = addr[0];
         a.bcy = addr[1];
         a.bcz = addr[2];
-        a.bcv = bcv;
     }
     int dev = 0;
     if (ep) {
@@ -646,6 +651,15 @@ pw_status pw_advect_adjoint(const pw_grid *grid, const pw_layout *layout, pw_dty
 
 namespace {
 
+pw_status check_adjoint_on_device(const AdjArgs &a) {
+    const char *names[] = {"u", "v", "w", "gsu", "gsv", "gsw", "gu", "gv", "gw", "tzc1", "tzc2", "tzd1", "tzd2"};
+    const void *ptrs[] = {a.u, a.v, a.w, a.gsu, a.gsv, a.gsw, a.gu, a.gv, a.gw, a.tzc1, a.tzc2, a.tzd1, a.tzd2};
+    int dev = 0;
+    PW_TRY(current_device(&dev));
+    for (int i = 0; i < 13; ++i) PW_TRY(check_on_device(names[i], ptrs[i], dev));
+    return PW_OK;
+}
+
 // Validation of the adjoint's operands; fills `a` and the resolved layout.
 pw_status check_adjoint(const pw_grid *grid, const pw_layout *layout, pw_dtype dtype,
                         const void *u, const void *v, const void *w, const pw_coeffs *coeffs,
@@ -679,12 +693,6 @@ pw_status check_adjoint(const pw_grid *grid, const pw_layout *layout, pw_dtype d
     if (tile && !adjoint_tile_supported(to_cfg(*tile)))
         return fail(PW_ERR_INVALID_ARG, "unsupported adjoint tile cols=%d rows=%d zlen=%d waves=%d prefetch=%d",
                     tile->cols_per_lane, tile->rows_per_strip, tile->zlen, tile->waves_per_group, tile->prefetch);
-    if (device) {
-        int dev = 0;
-        PW_TRY(current_device(&dev));
-        for (int i = 0; i < 13; ++i) PW_TRY(check_on_device(names[i], ptrs[i], dev));
-    }
-
     AdjArgs a;
     a.u = u; a.v = v; a.w = w;
     a.gsu = gsu; a.gsv = gsv; a.gsw = gsw;
@@ -693,6 +701,7 @@ pw_status check_adjoint(const pw_grid *grid, const pw_layout *layout, pw_dtype d
     a.tcx = coeffs->tcx; a.tcy = coeffs->tcy;
     a.nx = grid->nx; a.ny = grid->ny; a.nz = grid->nz; a.h = grid->halo;
     a.in_sy = L.in_sy; a.in_sz = L.in_sz; a.out_sy = L.out_sy; a.out_sz = L.out_sz;
+    if (device) PW_TRY(check_adjoint_on_device(a));
     *aout = a;
     *Lout = L;
     return PW_OK;
@@ -718,6 +727,47 @@ pw_status pw_advect_adjoint_ex(const pw_grid *grid, const pw_layout *layout, pw_
         cfg = default_adjoint_tile(a, dtype), how = "default";
     log_launch("pw_advect_adjoint", grid, dtype, &cfg, how);
     return launch_adjoint(a, dtype, cfg, static_cast<hipStream_t>(hip_stream));
+}
+
+pw_status pw_advect_bc_adjoint(const pw_grid *grid, const pw_layout *layout, pw_dtype dtype,
+                               const void *u, const void *v, const void *w, const pw_coeffs *coeffs,
+                               const pw_halo_modes bc[3], const void *gsu, const void *gsv, const void *gsw,
+                               void *gu, void *gv, void *gw, const pw_tile *tile, void *hip_stream) {
+    g_err[0] = 0;
+    if (!bc) return fail(PW_ERR_INVALID_ARG, "bc is NULL");
+    AdjArgs a;
+    Layout L;
+    PW_TRY(check_adjoint(grid, layout, dtype, u, v, w, coeffs, gsu, gsv, gsw, gu, gv, gw, tile, &a, &L, false));
+    int32_t addr[3];
+    PW_TRY(boundary_rules(grid, bc, addr, &a.bcv));
+    a.bcx = addr[0];
+    a.bcy = addr[1];
+    a.bcz = addr[2];
+    PW_TRY(check_adjoint_on_device(a));
+    TileCfg cfg;
+    const char *how = "given";
+    if (tile)
+        cfg = to_cfg(*tile);
+    else if (lookup_tuned(TuneKind::Adjoint, grid, dtype, &cfg))
+        how = "tuned";
+    else
+        cfg = default_adjoint_tile(a, dtype), how = "default";
+    log_launch("pw_advect_bc_adjoint", grid, dtype, &cfg, how);
+    PW_TRY(launch_adjoint_bc(a, dtype, cfg, static_cast<hipStream_t>(hip_stream)));
+    HaloArgs f{};
+    void *const g[3] = {gu, gv, gw};
+    f.nf = 3;
+    f.es = static_cast<int32_t>(elem_size(dtype));
+    f.nx = grid->nx; f.ny = grid->ny; f.nz = grid->nz; f.h = grid->halo;
+    f.sy = L.in_sy;
+    f.sz = L.in_sz;
+    for (int i = 0; i < 3; ++i) {
+        f.f[i] = g[i];
+        f.mode[i][0] = bc[i].x;
+        f.mode[i][1] = bc[i].y;
+        f.mode[i][2] = bc[i].z;
+    }
+    return launch_halo_fold(f, static_cast<hipStream_t>(hip_stream));
 }
 
 pw_status pw_advect_adjoint_coeff_grad(const pw_grid *grid, const pw_layout *layout, pw_dtype dtype,

@@ -70,6 +70,9 @@ struct AdjArgs {
     int64_t nx, ny, nz;
     int32_t h;
     int64_t in_sy, in_sz, out_sy, out_sz;
+    // boundary rules by addressing (launch_adjoint_bc), as FwdArgs' bcx ... bcv
+    int32_t bcx = PW_HALO_KEEP, bcy = PW_HALO_KEEP, bcz = PW_HALO_KEEP;
+    uint32_t bcv = 0;
 };
 
 // Operands of one tangent launch: the forward's (outputs tu, tv, tw in su, sv,
@@ -133,6 +136,10 @@ pw_status launch_forward_lds_f64(const FwdArgs &a, const TileCfg &cfg, hipStream
 pw_status launch_forward_lds_bf16(const FwdArgs &a, const TileCfg &cfg, hipStream_t s);
 pw_status launch_forward_lds_f16(const FwdArgs &a, const TileCfg &cfg, hipStream_t s);
 pw_status launch_adjoint(const AdjArgs &a, pw_dtype dt, const TileCfg &cfg, hipStream_t s);
+// The gradients with u, v, w read through the boundary rules of a.bcx ... a.bcv
+// (the adjoint at the filled state; gradients of the halo cells are left in the
+// halo, for launch_halo_fold).
+pw_status launch_adjoint_bc(const AdjArgs &a, pw_dtype dt, const TileCfg &cfg, hipStream_t s);
 // The adjoint march computing the wind gradients (grads), the per-strip
 // coefficient partials (partials != NULL: [6][nz][adjoint_strips(g, cfg.ry)]
 // doubles), or both in one pass; the coefficient fields of `a` are only read

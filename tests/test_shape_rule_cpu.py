@@ -38,3 +38,19 @@ def test_picks_are_supported_shapes(kind, dtypes):
             st = lib.pw_advect_ex(ctypes.byref(B.pw_grid(nx, ny, nz, 1)), None, code, a, a + mb, a + 2 * mb,
                                   ctypes.byref(c), a + 3 * mb, a + 4 * mb, a + 5 * mb, ctypes.byref(B.pw_tile(*t)), None)
             assert st in (B.PW_ERR_NO_DEVICE, B.PW_ERR_INVALID_ARG) and "tile" not in B.pw_last_error(), (t, st)
+
+
+def test_which_boundary_gradients_read_through_the_rules():
+    p = [tuple(B.HALO_MODES[m] for m in ("periodic", "copy", "zero"))] * 3
+    x = [torch.zeros(5, 6, 7) for _ in range(3)]
+    goes = B._bc_adjoint_reads_through
+    assert goes(*x, p) and goes(*[t.double() for t in x], p)
+    assert goes(*x, p[:2] + [(1, 5, 2)])                      # copy / reflect_neg, zero / copy: all nearest-cell
+    for codes in (p[:2] + [(0, 2, 3)], p[:2] + [(1, 1, 3)], [(9, 9, 9)] * 3):
+        assert not goes(*x, codes)
+    assert not goes(*[t.bfloat16() for t in x], p)            # no such adjoint
+    assert not goes(x[0], x[1], x[2].double(), p)
+    assert not goes(*[torch.zeros(5, 6, 9)[:, :, :7] for _ in range(3)], p)
+    assert not goes(*[torch.zeros(7, 6, 5).permute(2, 1, 0) for _ in range(3)], p)
+    assert not goes(x[0], x[1], torch.zeros(5, 6, 8)[:, :, :7], p)
+    assert not goes(*[torch.zeros(6, 7) for _ in range(3)], p)
