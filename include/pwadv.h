@@ -125,9 +125,11 @@ pw_status pw_advect(const pw_grid *grid, const pw_layout *layout, pw_dtype in_dt
  * Adjoint (pw_advect_adjoint_ex): cols_per_lane 1 (strips of 62 padded
  *   columns), rows_per_strip in {1, 2, 4}, prefetch 0, 1 or 2.
  * Batched form: as the forward with cols_per_lane <= 4 (FP32), prefetch 0, 1 or 2;
- *   or cols_per_lane 0: per subdomain 2 where that leaves no more lanes idle
- *   than 1 (nx rounded up to 128 equals nx rounded up to 64), else 1, with
- *   rows_per_strip in {1, 2, 4}; share_rows 0.
+ *   or cols_per_lane 0, chosen per subdomain: with rows_per_strip 4 one, two
+ *   or four columns, the narrowest strip that spans nx (above 128 columns four,
+ *   in strips of two rows); with rows_per_strip 1 or 2 two columns where that
+ *   leaves no more lanes idle than one (nx rounded up to 128 equals nx rounded
+ *   up to 64), else one; share_rows 0.
  * Tangent: prefetch 0, 1 or 2.
  * Tangent (pw_advect_tangent_ex): cols_per_lane 1 or 2 (PW_F64: 1),
  *   rows_per_strip in {1, 2}.

@@ -51,8 +51,13 @@ __global__ void batch_reset_kernel(unsigned long long *counter) {
 
 // Depth: planes in flight (1 or 2).  MaxT: workgroup size bound (built for
 // 256 and 512 threads, as the single-grid kernels).  PX 0: each subdomain's
-// strips have the width its work-list entry names (1 or 2 columns per lane;
-// the choice is wave-uniform, made per work item).
+// strips have the width its work-list entry names (1, 2 or 4 columns per lane;
+// the choice is wave-uniform, made per work item), four-column ones two rows
+// where the tile says four.
+// Rows of a strip of px columns per lane where the tile says ry and leaves the
+// columns to the subdomain (four columns hold two rows in registers).
+__host__ __device__ constexpr int sub_rows(int px, int ry) { return px == 4 && ry > 2 ? 2 : ry; }
+
 template <typename Tin, int PX, int RY, int Depth, int MaxT>
 __global__ __launch_bounds__(MaxT) void pw_batch_kernel(const BatchSub<Tin> *__restrict__ subs, int nsub,
                                                        int64_t nitems, unsigned long long *counter) {
@@ -83,7 +88,10 @@ __global__ __launch_bounds__(MaxT) void pw_batch_kernel(const BatchSub<Tin> *__r
         const int tx = static_cast<int>(t2 % a.ntx);
         const int ty = static_cast<int>(t2 / a.ntx);
         if constexpr (PX == 0) {
-            if (subs[lo].px == 2)
+            const int px = subs[lo].px;
+            if (RY == 4 && px == 4)
+                strip_march<Tin, 4, sub_rows(4, RY), Depth>(a, tx, ty, cz);
+            else if (px == 2)
                 strip_march<Tin, 2, RY, Depth>(a, tx, ty, cz);
             else
                 strip_march<Tin, 1, RY, Depth>(a, tx, ty, cz);
@@ -134,15 +142,14 @@ hipError_t launch_batch(const TileCfg &c, dim3 g, dim3 b, hipStream_t s, const B
     return hipLaunchKernel(k, g, b, args, 0, s);
 }
 
-// Shape of a batch of `points` points.  Large batches: four columns per lane
-// with two planes in flight; small ones, whose tail counts, many short items of
-// the width that suits each subdomain.  Measured on uneven subdomains, the two
-// shapes and the fixed one they replace (1, 2, 64, 4, 1): 64 subdomains (213 M
-// points) 1.28, 1.29 and 1.70 ms; 24 (105 M) 0.61, 0.66 and 0.86 ms; 8 (20 M)
-// 0.185, 0.162 and 0.204 ms.
-TileCfg default_batch_tile(int64_t points) {
-    return points >= 48000000 ? TileCfg{4, 2, 64, 4, 2, 0} : TileCfg{0, 4, 16, 4, 1, 0};
-}
+// Shape of a batch of `points` points: four-row strips of the width that suits
+// each subdomain (four columns: two rows), one plane ahead.  Longer items where
+// the batch is large enough that its tail does not count.  Measured on uneven
+// subdomains, chunks of 32 and of 16 levels and four columns for all (two rows,
+// 64 levels, two planes ahead): 64 subdomains (213 M points) 1.10, 1.13 and
+// 1.32 ms; 32 (88 M) 0.50, 0.51 and 0.64 ms; 8 (40 M) 0.236, 0.230 and 0.245
+// ms; 4 (8 M) 0.064, 0.067 and 0.109 ms.
+TileCfg default_batch_tile(int64_t points) { return TileCfg{0, 4, points >= 48000000 ? 32 : 16, 4, 1, 0}; }
 
 }  // namespace
 }  // namespace pw
@@ -172,11 +179,17 @@ void drop_graph(pw_batch *b) {
     b->graph = nullptr;
 }
 
-// Columns per lane of a subdomain nx wide under the per-subdomain choice:
-// 2 where that leaves no more lanes idle than 1 (fewer, wider vector loads
-// per point), else 1 (e.g. 33..64 or 129..192 columns: half a 128-column
-// strip would be empty).
-int sub_columns(int64_t nx) {
+// Columns per lane of a subdomain nx wide under the per-subdomain choice.
+// Tiles of four rows: the narrowest strip that spans it, four columns above
+// 128.  Batches of equal widths, TB/s of the operator's bytes with 1 / 2 columns
+// (four rows) and 4 (two rows), chunks of 32 levels: 40 columns 3.9 / 2.5 / 1.2,
+// 64 4.3 / 3.4 / 1.9, 66 3.2 / 3.3 / 1.9, 100 3.1 / 3.7 / 2.8, 128 3.8 / 4.1 /
+// 3.6, 150 3.0 / 2.9 / 3.7, 220 3.1 / 3.1 / 4.1, 256 3.8 / 3.9 / 4.5, 400 3.4 /
+// 3.8 / 4.3, 700 3.6 / 3.9 / 4.5 (320, two and a half strips, 4.0 / 4.3 / 4.0).
+// Fewer rows: 2 where that leaves no more lanes idle than 1 (fewer, wider
+// vector loads per point), else 1.
+int sub_columns(int64_t nx, int ry) {
+    if (ry == 4) return nx <= 64 ? 1 : nx <= 128 ? 2 : 4;
     const int64_t s1 = (nx + 63) / 64 * 64, s2 = (nx + 127) / 128 * 128;
     return s2 == s1 ? 2 : 1;
 }
@@ -208,10 +221,11 @@ pw_status build_table(pw_batch *b, const TileCfg &tile) {
         a.out_sz = g.out_sz;
         a.in_sy = static_cast<int32_t>(g.in_sy);
         a.out_sy = static_cast<int32_t>(g.out_sy);
-        const int px = tile.px > 0 ? tile.px : sub_columns(g.nx);
+        const int px = tile.px > 0 ? tile.px : sub_columns(g.nx, tile.ry);
         h[i].px = px;
         a.ntx = static_cast<int32_t>((g.nx + 64 * px - 1) / (64 * px));
-        a.nty = static_cast<int32_t>((g.ny + tile.ry - 1) / tile.ry);
+        const int ry = tile.px > 0 ? tile.ry : sub_rows(px, tile.ry);
+        a.nty = static_cast<int32_t>((g.ny + ry - 1) / ry);
         // split nz evenly into chunks of at most tile.zlen levels
         const int64_t chunks = (g.nz + tile.zlen - 1) / tile.zlen;
         a.zlen = static_cast<int32_t>((g.nz + chunks - 1) / chunks);
@@ -260,10 +274,14 @@ pw_status enqueue(pw_batch *b, hipStream_t s) {
 bool batch_tile_ok(const TileCfg &c) {
     if (c.zlen < 1 || c.share != 0) return false;
     if (c.px == 0) {
-        TileCfg c1 = c, c2 = c;
-        c1.px = 1;
-        c2.px = 2;
-        return tile_supported(c1, PW_F32) && tile_supported(c2, PW_F32) && batch_kernel(c) != nullptr;
+        for (int px : {1, 2, 4}) {
+            if (px == 4 && c.ry != 4) continue;
+            TileCfg cp = c;
+            cp.px = px;
+            cp.ry = sub_rows(px, c.ry);
+            if (!tile_supported(cp, PW_F32)) return false;
+        }
+        return batch_kernel(c) != nullptr;
     }
     return tile_supported(c, PW_F32) && batch_kernel(c) != nullptr;
 }
