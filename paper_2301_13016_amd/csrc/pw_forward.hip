@@ -136,17 +136,21 @@ bool tile_supported(const TileCfg &c, pw_dtype dt) {
 }
 
 TileCfg default_forward_tile(const FwdArgs &a, pw_dtype dt) {
-    // Narrow grids: one column per lane.  Wide ones: 16 bytes per lane with
-    // shared rows -- a short workgroup (two wavefronts of one row, FP32) while
-    // the grid is small enough that wavefronts in flight decide, tall ones
-    // (four wavefronts of two rows, half the rows read twice) where the bytes
-    // do.  Measured, tall against short: 512x512x64 (aligned rows) 69.4 / 82.6
-    // us, 415x420x169 155 / 177, 1000x300x64 106 / 117, but 96.5 / 98.6 at
+    // Narrow and ragged grids: one column per lane, counted as packed strips
+    // (see strip_march_t) in FP32 and 16-bit storage: against the shapes that
+    // plain strips made cheapest FP32 267x185x66 31.3 -> 25.3 us, 337x713x26
+    // 46.4 -> 40.4, BF16 78x230x187 29.8 -> 23.1 (FP64's two-column strips hold
+    // their own: 66x200x200 27.6 us, packed 37).  Wide ones: 16 bytes per lane
+    // with shared rows -- a short workgroup (two wavefronts of one row, FP32)
+    // while the grid is small enough that wavefronts in flight decide, tall
+    // ones (four wavefronts of two rows, half the rows read twice) where the
+    // bytes do.  Measured, tall against short: 512x512x64 (aligned rows) 69.4 /
+    // 82.6 us, 415x420x169 155 / 177, 1000x300x64 106 / 117, but 96.5 / 98.6 at
     // 536x186x162 and 34.7 / 35.4 at 250x250x100; FP64 250x250x100 63 / 69,
     // 201x143x117 46 / 42.
     const int64_t pts = a.nx * a.ny * a.nz;
     if (dt == PW_F32) {
-        static const ShapeCost small[] = {{1, 2, 1, 1, 0, 64, 2048, 0.90}, {1, 4, 1, 1, 0, 64, 2048, 1.50},
+        static const ShapeCost small[] = {{1, 2, 1, 1, 0, 64, 2048, 0.90, true}, {1, 4, 1, 1, 0, 64, 2048, 1.50, true},
                                           {4, 1, 2, 1, 2, 256, 2048, 0.95}};
         static const ShapeCost large[] = {{1, 4, 1, 1, 0, 64, 2048, 1.50}, {4, 2, 4, 1, 2, 256, 1024, 1.35}};
         return pts < 16000000 ? cheapest_shape(small, 3, a.nx, a.ny, a.nz)
@@ -159,7 +163,7 @@ TileCfg default_forward_tile(const FwdArgs &a, pw_dtype dt) {
         return pts < 5000000 ? cheapest_shape(small, 3, a.nx, a.ny, a.nz)
                              : cheapest_shape(large, 2, a.nx, a.ny, a.nz);
     }
-    static const ShapeCost small[] = {{1, 2, 1, 1, 0, 64, 2048, 0.67}, {1, 4, 1, 1, 0, 64, 2048, 1.09},
+    static const ShapeCost small[] = {{1, 2, 1, 1, 0, 64, 2048, 0.67, true}, {1, 4, 1, 1, 0, 64, 2048, 1.09, true},
                                       {2, 2, 1, 1, 0, 128, 2048, 0.97}, {4, 2, 2, 1, 1, 256, 2048, 1.58}};
     static const ShapeCost large[] = {{1, 4, 1, 1, 0, 64, 2048, 1.09}, {4, 4, 2, 1, 2, 256, 1024, 2.00}};
     return pts < 64000000 ? cheapest_shape(small, 4, a.nx, a.ny, a.nz)

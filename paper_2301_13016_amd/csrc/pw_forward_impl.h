@@ -53,7 +53,7 @@ using namespace dev;
 // built twice: for up to 256 threads (four wavefronts, one per SIMD, so a
 // wavefront may use the whole 512-entry register file: the large strips keep
 // their planes in registers instead of spilling) and for up to 512.
-template <typename Tin, int PX, int RY, int Depth, int Epi, int Bc, int MaxT>
+template <typename Tin, int PX, int RY, int Depth, int Epi, int Bc, int MaxT, bool Pack = false>
 __global__ __launch_bounds__(MaxT) void pw_forward_kernel(FwdK<Tin> a) {
     // wavefront index as a scalar, so that per-strip conditions stay scalar
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
@@ -63,7 +63,10 @@ __global__ __launch_bounds__(MaxT) void pw_forward_kernel(FwdK<Tin> a) {
     const int tx = t2 % a.ntx;
     const int ty = (t2 / a.ntx) * a.wpb + wave;
     if (ty >= a.nty) return;   // whole wavefront
-    strip_march<Tin, PX, RY, Depth, Epi, Bc>(a, tx, ty, cz);
+    if constexpr (Pack)   // ntx = 1, pieces numbered through
+        strip_march<Tin, PX, RY, Depth, Epi, Bc, true>(a, ty, 0, cz);
+    else
+        strip_march<Tin, PX, RY, Depth, Epi, Bc>(a, tx, ty, cz);
 }
 
 // W wavefronts per workgroup sharing their edge rows through LDS (see
@@ -121,7 +124,16 @@ void launch_fwd_b(const FwdK<Tin> &a, const TileCfg &cfg, dim3 grid, dim3 block,
 }
 
 template <typename Tin, int PX, int RY, int Epi>
-void launch_fwd_k(const FwdK<Tin> &a, const TileCfg &cfg, dim3 grid, dim3 block, hipStream_t s) {
+void launch_fwd_k(const FwdK<Tin> &a, const TileCfg &cfg, bool pack, dim3 grid, dim3 block, hipStream_t s) {
+    if constexpr (PX == 1) {
+        if (pack) {   // built for one bound only
+            if (cfg.depth == 2 && Epi != kEpiSelf)
+                hipLaunchKernelGGL((pw_forward_kernel<Tin, PX, RY, 2, Epi, 0, 512, true>), grid, block, 0, s, a);
+            else
+                hipLaunchKernelGGL((pw_forward_kernel<Tin, PX, RY, 1, Epi, 0, 512, true>), grid, block, 0, s, a);
+            return;
+        }
+    }
     if (a.bcv != 0)
         launch_fwd_b<Tin, PX, RY, Epi, 2>(a, cfg, grid, block, s);
     else if (a.bcx != PW_HALO_KEEP || a.bcy != PW_HALO_KEEP || a.bcz != PW_HALO_KEEP)
@@ -172,7 +184,15 @@ FwdK<Tin> make_fwdk(const FwdArgs &g, const TileCfg &cfg) {
 
 template <typename Tin, int PX, int RY>
 pw_status launch_fwd_t(const FwdArgs &g, const TileCfg &cfg, hipStream_t s) {
-    const FwdK<Tin> a = make_fwdk<Tin, PX, RY>(g, cfg);
+    FwdK<Tin> a = make_fwdk<Tin, PX, RY>(g, cfg);
+    // packed strips where they are fewer (see strip_march_t)
+    const int64_t packed = packed_strips(g.nx, a.nty);
+    const bool pack = PX == 1 && packed < int64_t(a.ntx) * a.nty && g.bcv == 0 && g.bcx == PW_HALO_KEEP &&
+                      g.bcy == PW_HALO_KEEP && g.bcz == PW_HALO_KEEP;
+    if (pack) {
+        a.ntx = 1;
+        a.nty = static_cast<int32_t>(packed);
+    }
     const int64_t nblk_y = (a.nty + cfg.wpb - 1) / cfg.wpb;
     const int64_t nblocks = static_cast<int64_t>(a.ntx) * nblk_y * a.nzc;
     if (nblocks <= 0 || nblocks > 0x7fffffffLL) return fail(PW_ERR_UNSUPPORTED, "grid too large");
@@ -180,12 +200,12 @@ pw_status launch_fwd_t(const FwdArgs &g, const TileCfg &cfg, hipStream_t s) {
     bool self = false;
     if constexpr (sizeof(Tin) == sizeof(typename Storage<Tin>::Tc)) {
         self = cfg.wpb <= 4 && addends_are_fields<Tin>(g);
-        if (self) launch_fwd_k<Tin, PX, RY, kEpiSelf>(a, cfg, grid, block, s);
+        if (self) launch_fwd_k<Tin, PX, RY, kEpiSelf>(a, cfg, pack, grid, block, s);
     }
     if (g.epilogue && !self)
-        launch_fwd_k<Tin, PX, RY, kEpiLoad>(a, cfg, grid, block, s);
+        launch_fwd_k<Tin, PX, RY, kEpiLoad>(a, cfg, pack, grid, block, s);
     else if (!self)
-        launch_fwd_k<Tin, PX, RY, 0>(a, cfg, grid, block, s);
+        launch_fwd_k<Tin, PX, RY, 0>(a, cfg, pack, grid, block, s);
     return hip_fail(hipGetLastError(), "forward kernel launch");
 }
 

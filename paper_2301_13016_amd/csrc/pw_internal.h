@@ -108,7 +108,11 @@ struct ShapeCost {
     int cols;
     int slots;
     double cost;
+    bool packs = false;   // packed strips where they are fewer (see packed_strips)
 };
+// Strips of a grid whose blocks of rows are packed into wavefronts end to end,
+// each block n + 2 positions long (see strip_march_t and pw_zfast_impl.h).
+inline int64_t packed_strips(int64_t n, int64_t blocks) { return (blocks * (n + 2) - 1 + kWaveCols - 1) / kWaveCols; }
 // The cheapest of n shapes, march length included, for a grid of `lead`
 // elements along the lanes, `rows` rows and `march` levels.
 TileCfg cheapest_shape(const ShapeCost *s, int n, int64_t lead, int64_t rows, int64_t march, double start = 1.5);

@@ -28,6 +28,8 @@
 // of one level: a march of eight is latency, and the grid has too few strips
 // to hide it), 130 -> 42 us at 42x587x244 (one column per lane where four
 // leave 5 lanes in 6 idle), 70 -> 43 us at 300x300x75.
+#include <algorithm>
+
 #include "pw_internal.h"
 
 namespace pw {
@@ -38,8 +40,9 @@ TileCfg cheapest_shape(const ShapeCost *s, int n, int64_t lead, int64_t rows, in
     double best_cost = -1.0;
     const int levels = static_cast<int>(march);   // extents are at most 2^30 plus the halo
     for (int i = 0; i < n; ++i) {
-        const double strips = static_cast<double>((lead + s[i].cols - 1) / s[i].cols) *
-                              static_cast<double>((rows + s[i].ry - 1) / s[i].ry);
+        const int64_t blocks = (rows + s[i].ry - 1) / s[i].ry;
+        double strips = static_cast<double>((lead + s[i].cols - 1) / s[i].cols) * static_cast<double>(blocks);
+        if (s[i].packs) strips = std::min(strips, static_cast<double>(packed_strips(lead, blocks)));
         for (int c : kChunks) {
             if (c > levels) break;
             const int z = (levels + c - 1) / c, chunks = (levels + z - 1) / z;

@@ -306,7 +306,7 @@ __device__ __forceinline__ void bc_patch_x(Plane<Tin, PX, RY> &P, const StripAdd
     }
 }
 
-template <typename Tin, int PX, int RY, bool Full, int Bc = 0>
+template <typename Tin, int PX, int RY, bool Full, int Bc = 0, bool Pack = false>
 __device__ __forceinline__ void load_plane(Plane<Tin, PX, RY> &P, const FwdK<Tin> &a,
                                            int kp, const StripAddr<RY> &s, int last_col) {
     const int64_t pb = static_cast<int64_t>(kp) * a.in_sz * static_cast<int64_t>(sizeof(Tin));
@@ -320,9 +320,13 @@ __device__ __forceinline__ void load_plane(Plane<Tin, PX, RY> &P, const FwdK<Tin
         load_row<Tin, PX, Full, Bc>(P.v[r], bv, s.roff[r], lim, s.col, last_col, a.nx, a.h, a.bcx);
         load_row<Tin, PX, Full, Bc>(P.w[r], bw, s.roff[r], lim, s.col, last_col, a.nx, a.h, a.bcx);
     }
-    P.hu = PW_GLOAD(Tin, bu + s.hoff);
-    P.hv = PW_GLOAD(Tin, bv + s.hoff);
-    P.hw = PW_GLOAD(Tin, bw + s.hoff);
+    if constexpr (Pack) {   // no lane reads them
+        P.hu = P.hv = P.hw = Tin(0);
+    } else {
+        P.hu = PW_GLOAD(Tin, bu + s.hoff);
+        P.hv = PW_GLOAD(Tin, bv + s.hoff);
+        P.hw = PW_GLOAD(Tin, bw + s.hoff);
+    }
 }
 
 template <typename T, int N> __device__ __forceinline__ void store_vec(char *p, const T (&x)[N]) {
@@ -377,7 +381,8 @@ template <typename Tin, int PX, int RY> struct EpiRows {
     typename Vec<Tc, PX>::type u[RY], v[RY], w[RY];
 };
 
-template <typename Tin, int PX, int RY>
+// Packed strips read them with ordinary loads, as in load_zepi.
+template <typename Tin, int PX, int RY, bool Pack = false>
 __device__ __forceinline__ void load_epi(EpiRows<Tin, PX, RY> &E, const FwdK<Tin> &a, int kk,
                                          const uint32_t (&eoff)[RY]) {
     using Tc = typename Storage<Tin>::Tc;
@@ -388,9 +393,9 @@ __device__ __forceinline__ void load_epi(EpiRows<Tin, PX, RY> &E, const FwdK<Tin
     const char *bw = reinterpret_cast<const char *>(a.cw) + ob;
 #pragma unroll
     for (int r = 0; r < RY; ++r) {
-        E.u[r] = PW_GLOAD_NT(VT, bu + eoff[r]);
-        E.v[r] = PW_GLOAD_NT(VT, bv + eoff[r]);
-        E.w[r] = PW_GLOAD_NT(VT, bw + eoff[r]);
+        E.u[r] = Pack ? PW_GLOAD(VT, bu + eoff[r]) : PW_GLOAD_NT(VT, bu + eoff[r]);
+        E.v[r] = Pack ? PW_GLOAD(VT, bv + eoff[r]) : PW_GLOAD_NT(VT, bv + eoff[r]);
+        E.w[r] = Pack ? PW_GLOAD(VT, bw + eoff[r]) : PW_GLOAD_NT(VT, bw + eoff[r]);
     }
 }
 
@@ -573,16 +578,33 @@ __device__ __forceinline__ int xcd_tile(int b, int nb) {
 // start of the level, before that level's plane prefetch (a scheduling
 // barrier keeps the compiler from moving them after it), so waiting for them
 // never waits for the prefetch.
-template <typename Tin, int PX, int RY, bool Full, int Depth, int Epi, int Bc>
+//
+// Pack (one column per lane, no boundary rules): the row blocks of RY rows are
+// laid end to end, each with the column left and the column right of its rows,
+// and cut into pieces of 62 positions; tx numbers the pieces.  The wavefront
+// loads the 64 positions around its piece, so the lanes' neighbours are theirs
+// in the row too, and every row is read at its lane's own offset.  Rows that
+// fill few of a strip's 64 columns (75 of 128, 40 of 64) then leave no lanes
+// idle but each block's two and each piece's two.
+template <typename Tin, int PX, int RY, bool Full, int Depth, int Epi, int Bc, bool Pack = false>
 __device__ __forceinline__ void strip_march_t(const FwdK<Tin> &a, int tx, int ty, int cz) {
     using Tc = typename Storage<Tin>::Tc;
     const int lane = threadIdx.x & 63;
 
     const int pcols = a.nx + 2 * a.h, prows = a.ny + 2 * a.h;
     const int last_col = pcols - 1;
-    const int ii0 = tx * 64 * PX + lane * PX;        // first interior column of this lane
-    const int nvalid = a.nx - ii0;                    // its columns inside the grid (may be <= 0)
-    const int jj0 = ty * RY;
+    int ii0 = tx * 64 * PX + lane * PX;               // first interior column of this lane
+    int nvalid = a.nx - ii0;                          // its columns inside the grid (may be <= 0)
+    int jj0 = ty * RY;
+    if constexpr (Pack) {
+        static_assert(PX == 1 && !Full && Bc == 0, "packed strips have one column per lane and no boundary rules");
+        const int len = a.nx + 2, blocks = (a.ny + RY - 1) / RY;
+        const int at = min(tx * kWaveCols + lane, blocks * len - 1);
+        const int block = static_cast<int>(static_cast<uint32_t>(at) / static_cast<uint32_t>(len));
+        ii0 = at - block * len - 1;   // -1 .. nx
+        jj0 = block * RY;
+        nvalid = (lane >= 1 && lane <= kWaveCols && ii0 >= 0 && ii0 < a.nx) ? 1 : 0;
+    }
 
     StripAddr<RY> s;
     s.col = min(ii0 + a.h, last_col);
@@ -593,7 +615,8 @@ __device__ __forceinline__ void strip_march_t(const FwdK<Tin> &a, int tx, int ty
         const int prow = bc_map<Bc>(min(jj0 - 1 + a.h + r, prows - 1), a.ny, a.h, a.bcy);
         s.roff[r] = static_cast<uint32_t>((prow * a.in_sy + s.col) * static_cast<int>(sizeof(Tin)));
     }
-    {   // packed halo: lane r -> left halo of row r, lane 32+r -> right halo of row r
+    s.hoff = 0;
+    if constexpr (!Pack) {   // packed halo: lane r -> left halo of row r, lane 32+r -> right halo of row r
         const int hr = min(lane & 31, RY + 1);
         const int hrow_p = min(jj0 - 1 + a.h + hr, prows - 1);
         // (wide-lane strips at the x end under boundary rules: the first right-halo
@@ -614,11 +637,11 @@ __device__ __forceinline__ void strip_march_t(const FwdK<Tin> &a, int tx, int ty
     for (int r = 0; r < RY; ++r) {
         row_ok[r] = jj0 + r < a.ny;
         const int jj = min(jj0 + r, a.ny - 1);
-        const int ic = min(ii0, a.nx - 1);
+        const int ic = min(max(ii0, 0), a.nx - 1);
         ooff[r] = static_cast<uint32_t>((jj * a.out_sy + ic) * static_cast<int>(sizeof(Tc)));
-        eoff[r] = static_cast<uint32_t>((jj * a.out_sy + epi_col<PX>(ii0, a.nx)) * static_cast<int>(sizeof(Tc)));
+        eoff[r] = static_cast<uint32_t>((jj * a.out_sy + epi_col<PX>(PX == 1 ? ic : ii0, a.nx)) * static_cast<int>(sizeof(Tc)));
     }
-    const bool lane0 = lane == 0, lane63 = lane == 63;
+    const bool lane0 = !Pack && lane == 0, lane63 = !Pack && lane == 63;
     const uint32_t eshift = epi_off<PX>(ii0, a.nx);
 
     const int k0 = cz * a.zlen;
@@ -639,13 +662,13 @@ __device__ __forceinline__ void strip_march_t(const FwdK<Tin> &a, int tx, int ty
     } while (0)
 #define PW_PLOAD(P, kp)                                                                                        \
     do {                                                                                                       \
-        load_plane<Tin, PX, RY, Full, Bc>(P, a, bc_map<Bc>(min((kp), k1) + h, a.nz, h, a.bcz), s, last_col); \
+        load_plane<Tin, PX, RY, Full, Bc, Pack>(P, a, bc_map<Bc>(min((kp), k1) + h, a.nz, h, a.bcz), s, last_col); \
         P.zcode = bc_axis_code<Bc>(a.bcv, 2, min((kp), k1) + h, a.nz, h);                                      \
     } while (0)
 #define PW_LOAD(P, kp)                                                   \
     do {                                                                 \
         if constexpr (Epi == kEpiLoad) {                                 \
-            load_epi<Tin, PX, RY>(Ep, a, kk, eoff);                      \
+            load_epi<Tin, PX, RY, Pack>(Ep, a, kk, eoff);                      \
             __builtin_amdgcn_sched_barrier(0);                           \
         }                                                                \
         PW_PLOAD(P, kp);                                                 \
@@ -657,7 +680,7 @@ __device__ __forceinline__ void strip_march_t(const FwdK<Tin> &a, int tx, int ty
     } while (0)
 #define PW_FIRST(P, kp)                                                                            \
     do {                                                                                           \
-        load_plane<Tin, PX, RY, Full, Bc>(P, a, bc_map<Bc>((kp) + h, a.nz, h, a.bcz), s, last_col); \
+        load_plane<Tin, PX, RY, Full, Bc, Pack>(P, a, bc_map<Bc>((kp) + h, a.nz, h, a.bcz), s, last_col); \
         P.zcode = bc_axis_code<Bc>(a.bcv, 2, (kp) + h, a.nz, h);                                   \
     } while (0)
 #define PW_FIX_FIRST(A, B)                                   \
@@ -723,9 +746,11 @@ __device__ __forceinline__ void strip_march_t(const FwdK<Tin> &a, int tx, int ty
 }
 
 // Bc: reads go through the boundary rules a.bcx/bcy/bcz (pw_advect_bc).
-template <typename Tin, int PX, int RY, int Depth, int Epi = 0, int Bc = 0>
+template <typename Tin, int PX, int RY, int Depth, int Epi = 0, int Bc = 0, bool Pack = false>
 __device__ __forceinline__ void strip_march(const FwdK<Tin> &a, int tx, int ty, int cz) {
-    if constexpr (PX == 1) {
+    if constexpr (Pack) {
+        strip_march_t<Tin, PX, RY, false, Depth, Epi, Bc, true>(a, tx, ty, cz);
+    } else if constexpr (PX == 1) {
         // one-column lanes: loads never need clamping beyond the start column,
         // and one masked store per row is cheap, so one path serves every strip
         strip_march_t<Tin, PX, RY, false, Depth, Epi, Bc>(a, tx, ty, cz);

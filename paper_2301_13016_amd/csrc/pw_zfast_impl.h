@@ -37,6 +37,15 @@ namespace zf {
 
 using namespace dev;
 
+// Packed strips (one level per lane, Pack): the row blocks of RJ rows are laid
+// end to end, each with the level below and the level above its column, and
+// cut into pieces of 62 positions; a wavefront loads the 64 positions around
+// its piece, so the lanes' neighbours are theirs in the column too, and every
+// row is read at its lane's own offset.  A column that fills few of a strip's
+// 64 levels (75 of 128, 20 of 64) then leaves no lanes idle but the halo's two
+// and the piece's two.  Taken where that makes fewer strips (packed_strips).
+// FP32, best shapes: 300x300x75 66.3 -> 46.4 us, 500x300x20 23.5 -> 16.6,
+// 512x512x66 157 -> 112; with the epilogue 75.6 -> 60.9, 44.2 -> 27.2, 174 -> 151.
 template <typename Tin> struct ZfK {
     using Tc = typename Storage<Tin>::Tc;
     const Tin *u, *v, *w;
@@ -67,7 +76,7 @@ template <int RJ> struct ZAddr {
     uint32_t lim;            // largest offset of a vector in the array's last x-plane (see load_row)
 };
 
-template <typename Tin, int PZ, int RJ, bool Full>
+template <typename Tin, int PZ, int RJ, bool Full, bool Pack>
 __device__ __forceinline__ void load_xplane(ZPlane<Tin, PZ, RJ> &P, const ZfK<Tin> &a, int ip, const ZAddr<RJ> &s,
                                             int last_k) {
     const int64_t pb = static_cast<int64_t>(ip) * a.in_si * static_cast<int64_t>(sizeof(Tin));
@@ -81,9 +90,13 @@ __device__ __forceinline__ void load_xplane(ZPlane<Tin, PZ, RJ> &P, const ZfK<Ti
         load_row<Tin, PZ, Full>(P.v[r], bv, s.roff[r], lim, s.kcol, last_k, a.nz, a.h, PW_HALO_KEEP);
         load_row<Tin, PZ, Full>(P.w[r], bw, s.roff[r], lim, s.kcol, last_k, a.nz, a.h, PW_HALO_KEEP);
     }
-    P.hu = PW_GLOAD(Tin, bu + s.hoff);
-    P.hv = PW_GLOAD(Tin, bv + s.hoff);
-    P.hw = PW_GLOAD(Tin, bw + s.hoff);
+    if constexpr (Pack) {   // no lane reads them
+        P.hu = P.hv = P.hw = Tin(0);
+    } else {
+        P.hu = PW_GLOAD(Tin, bu + s.hoff);
+        P.hv = PW_GLOAD(Tin, bv + s.hoff);
+        P.hw = PW_GLOAD(Tin, bw + s.hoff);
+    }
 }
 
 template <typename Tc, int PZ> struct LaneCoeffs {
@@ -96,7 +109,10 @@ template <typename Tc, int PZ, int RJ> struct ZEpi {
     typename Vec<Tc, PZ>::type u[RJ], v[RJ], w[RJ];
 };
 
-template <typename Tin, int PZ, int RJ>
+// Packed strips read them with ordinary loads: their rows end inside a cache
+// line that another wavefront's rows need too (300x300x75 FP32: 68.3 us with
+// non-temporal loads, 64.5).
+template <typename Tin, int PZ, int RJ, bool Pack>
 __device__ __forceinline__ void load_zepi(ZEpi<typename Storage<Tin>::Tc, PZ, RJ> &E, const ZfK<Tin> &a, int ii,
                                           const uint32_t (&eoff)[RJ]) {
     using Tc = typename Storage<Tin>::Tc;
@@ -107,9 +123,9 @@ __device__ __forceinline__ void load_zepi(ZEpi<typename Storage<Tin>::Tc, PZ, RJ
     const char *bw = reinterpret_cast<const char *>(a.cw) + ob;
 #pragma unroll
     for (int r = 0; r < RJ; ++r) {
-        E.u[r] = PW_GLOAD_NT(VT, bu + eoff[r]);
-        E.v[r] = PW_GLOAD_NT(VT, bv + eoff[r]);
-        E.w[r] = PW_GLOAD_NT(VT, bw + eoff[r]);
+        E.u[r] = Pack ? PW_GLOAD(VT, bu + eoff[r]) : PW_GLOAD_NT(VT, bu + eoff[r]);
+        E.v[r] = Pack ? PW_GLOAD(VT, bv + eoff[r]) : PW_GLOAD_NT(VT, bv + eoff[r]);
+        E.w[r] = Pack ? PW_GLOAD(VT, bw + eoff[r]) : PW_GLOAD_NT(VT, bw + eoff[r]);
     }
 }
 
@@ -248,15 +264,26 @@ __device__ __forceinline__ void column(const ZPlane<Tin, PZ, RJ> &m, const ZPlan
 // lies wholly inside the grid ((tk+1)*64*PZ <= nz), so every lane loads
 // owns PZ outputs; otherwise vectors may run past the column's end (see load_row)
 // and each lane stores only its levels inside the grid.
-template <typename Tin, int PZ, int RJ, bool Full, int Depth, bool Epi>
+template <typename Tin, int PZ, int RJ, bool Full, int Depth, bool Epi, bool Pack>
 __device__ __forceinline__ void xmarch(const ZfK<Tin> &a, int tk, int ty, int cx) {
     using Tc = typename Storage<Tin>::Tc;
     const int lane = threadIdx.x & 63;
     const int plev = a.nz + 2 * a.h, prows = a.ny + 2 * a.h;
     const int last_k = plev - 1;
-    const int kk0 = tk * 64 * PZ + lane * PZ;   // first interior level of this lane
-    const int nvalid = a.nz - kk0;
-    const int jj0 = ty * RJ;
+    int kk0 = tk * 64 * PZ + lane * PZ;   // first interior level of this lane
+    int nvalid = a.nz - kk0;
+    int jj0 = ty * RJ;
+    if constexpr (Pack) {
+        static_assert(PZ == 1 && !Full, "packed strips have one level per lane");
+        // position of the lane in the row blocks laid end to end, each nz + 2
+        // levels long; lanes 1..62 own outputs
+        const int len = a.nz + 2, blocks = (a.ny + RJ - 1) / RJ;
+        const int at = min(tk * kWaveCols + lane, blocks * len - 1);
+        const int block = static_cast<int>(static_cast<uint32_t>(at) / static_cast<uint32_t>(len));
+        kk0 = at - block * len - 1;   // -1 .. nz
+        jj0 = block * RJ;
+        nvalid = (lane >= 1 && lane <= kWaveCols && kk0 >= 0 && kk0 < a.nz) ? 1 : 0;
+    }
 
     ZAddr<RJ> s;
     s.kcol = min(kk0 + a.h, last_k);
@@ -265,7 +292,8 @@ __device__ __forceinline__ void xmarch(const ZfK<Tin> &a, int tk, int ty, int cx
         const int prow = min(jj0 - 1 + a.h + r, prows - 1);
         s.roff[r] = static_cast<uint32_t>((prow * a.in_sj + s.kcol) * static_cast<int>(sizeof(Tin)));
     }
-    {   // packed halo: lane r -> level below row r, lane 32+r -> level above row r
+    s.hoff = 0;
+    if constexpr (!Pack) {   // packed halo: lane r -> level below row r, lane 32+r -> level above row r
         const int hr = min(lane & 31, RJ + 1);
         const int hrow = min(jj0 - 1 + a.h + hr, prows - 1);
         const int hk = (lane & 32) ? min(tk * 64 * PZ + 64 * PZ + a.h, last_k) : tk * 64 * PZ + a.h - 1;
@@ -274,25 +302,25 @@ __device__ __forceinline__ void xmarch(const ZfK<Tin> &a, int tk, int ty, int cx
     s.lim = static_cast<uint32_t>(((prows - 1) * a.in_sj + plev - PZ) * static_cast<int>(sizeof(Tin)));
     uint32_t ooff[RJ], eoff[RJ];
     bool row_ok[RJ];
-    const int kc = min(kk0, a.nz - 1);
+    const int kc = min(max(kk0, 0), a.nz - 1);
     const uint32_t eshift = epi_off<PZ>(kk0, a.nz);
 #pragma unroll
     for (int r = 0; r < RJ; ++r) {
         row_ok[r] = jj0 + r < a.ny;
         const int jj = min(jj0 + r, a.ny - 1);
         ooff[r] = static_cast<uint32_t>((jj * a.out_sj + kc) * static_cast<int>(sizeof(Tc)));
-        eoff[r] = static_cast<uint32_t>((jj * a.out_sj + epi_col<PZ>(kk0, a.nz)) * static_cast<int>(sizeof(Tc)));
+        eoff[r] = static_cast<uint32_t>((jj * a.out_sj + epi_col<PZ>(PZ == 1 ? kc : kk0, a.nz)) * static_cast<int>(sizeof(Tc)));
     }
     LaneCoeffs<Tc, PZ> K;
 #pragma unroll
     for (int x = 0; x < PZ; ++x) {
-        const int kq = min(kk0 + x, a.nz - 1);
+        const int kq = PZ == 1 ? kc : min(kk0 + x, a.nz - 1);
         K.z1[x] = PW_GLOAD(Tc, a.tzc1 + kq);
         K.z2[x] = PW_GLOAD(Tc, a.tzc2 + kq);
         K.d1[x] = PW_GLOAD(Tc, a.tzd1 + kq);
         K.d2[x] = PW_GLOAD(Tc, a.tzd2 + kq);
     }
-    const bool lane0 = lane == 0, lane63 = lane == 63;
+    const bool lane0 = !Pack && lane == 0, lane63 = !Pack && lane == 63;
 
     const int i0 = cx * a.xlen;
     const int i1 = min(a.nx, i0 + a.xlen);
@@ -308,17 +336,17 @@ __device__ __forceinline__ void xmarch(const ZfK<Tin> &a, int tk, int ty, int cx
 #define PW_XLOAD(P, ip)                                                      \
     do {                                                                     \
         if constexpr (Epi) {                                                 \
-            load_zepi<Tin, PZ, RJ>(Ep, a, ii, eoff);                         \
+            load_zepi<Tin, PZ, RJ, Pack>(Ep, a, ii, eoff);                         \
             __builtin_amdgcn_sched_barrier(0);                               \
         }                                                                    \
-        load_xplane<Tin, PZ, RJ, Full>(P, a, min((ip), i1) + h, s, last_k); \
+        load_xplane<Tin, PZ, RJ, Full, Pack>(P, a, min((ip), i1) + h, s, last_k); \
     } while (0)
-#define PW_XPLOAD(P, ip) load_xplane<Tin, PZ, RJ, Full>(P, a, min((ip), i1) + h, s, last_k)
+#define PW_XPLOAD(P, ip) load_xplane<Tin, PZ, RJ, Full, Pack>(P, a, min((ip), i1) + h, s, last_k)
 #define PW_COL(M, C, P) column<Tin, PZ, RJ, Full, Epi>(M, C, P, a, ii, lane0, lane63, nvalid, ooff, row_ok, K, Ep, eshift)
     int ii = i0;
     if constexpr (Depth == 1) {
         ZPlane<Tin, PZ, RJ> A, B, C, D;
-        load_xplane<Tin, PZ, RJ, Full>(A, a, i0 - 1 + h, s, last_k);
+        load_xplane<Tin, PZ, RJ, Full, Pack>(A, a, i0 - 1 + h, s, last_k);
         PW_XPLOAD(B, i0);
         PW_XPLOAD(C, i0 + 1);
         for (;;) {
@@ -339,7 +367,7 @@ __device__ __forceinline__ void xmarch(const ZfK<Tin> &a, int tk, int ty, int cx
         // five-plane ring: x-planes ii+2 and ii+3 in flight
         static_assert(Depth == 2, "prefetch depth 1 or 2");
         ZPlane<Tin, PZ, RJ> A, B, C, D, E;
-        load_xplane<Tin, PZ, RJ, Full>(A, a, i0 - 1 + h, s, last_k);
+        load_xplane<Tin, PZ, RJ, Full, Pack>(A, a, i0 - 1 + h, s, last_k);
         PW_XPLOAD(B, i0);
         PW_XPLOAD(C, i0 + 1);
         PW_XPLOAD(D, i0 + 2);
@@ -366,7 +394,7 @@ __device__ __forceinline__ void xmarch(const ZfK<Tin> &a, int tk, int ty, int cx
 #undef PW_COL
 }
 
-template <typename Tin, int PZ, int RJ, int Depth, bool Epi, int MaxT>
+template <typename Tin, int PZ, int RJ, int Depth, bool Epi, int MaxT, bool Pack>
 __global__ __launch_bounds__(MaxT) void pw_zfast_kernel(ZfK<Tin> a) {
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int t = xcd_tile(blockIdx.x, gridDim.x);
@@ -375,25 +403,30 @@ __global__ __launch_bounds__(MaxT) void pw_zfast_kernel(ZfK<Tin> a) {
     const int tk = t2 % a.nkc;
     const int ty = (t2 / a.nkc) * a.wpb + wave;
     if (ty >= a.nty) return;   // whole wavefront
-    if ((tk + 1) * 64 * PZ <= a.nz)
-        xmarch<Tin, PZ, RJ, true, Depth, Epi>(a, tk, ty, cx);
+    if constexpr (Pack)
+        xmarch<Tin, PZ, RJ, false, Depth, Epi, true>(a, ty, 0, cx);   // nkc = 1, strips numbered through
+    else if ((tk + 1) * 64 * PZ <= a.nz)
+        xmarch<Tin, PZ, RJ, true, Depth, Epi, false>(a, tk, ty, cx);
     else
-        xmarch<Tin, PZ, RJ, false, Depth, Epi>(a, tk, ty, cx);
+        xmarch<Tin, PZ, RJ, false, Depth, Epi, false>(a, tk, ty, cx);
 }
 
+template <typename Tin, int PZ, int RJ, bool Epi, int MaxT, bool Pack>
+void launch_m(const ZfK<Tin> &a, const TileCfg &cfg, dim3 grid, dim3 block, hipStream_t s) {
+    if (cfg.depth == 2)
+        hipLaunchKernelGGL((pw_zfast_kernel<Tin, PZ, RJ, 2, Epi, MaxT, Pack>), grid, block, 0, s, a);
+    else
+        hipLaunchKernelGGL((pw_zfast_kernel<Tin, PZ, RJ, 1, Epi, MaxT, Pack>), grid, block, 0, s, a);
+}
 template <typename Tin, int PZ, int RJ, bool Epi>
-void launch_k(const ZfK<Tin> &a, const TileCfg &cfg, dim3 grid, dim3 block, hipStream_t s) {
-    if (cfg.depth == 2) {
-        if (cfg.wpb <= 4)
-            hipLaunchKernelGGL((pw_zfast_kernel<Tin, PZ, RJ, 2, Epi, 256>), grid, block, 0, s, a);
-        else
-            hipLaunchKernelGGL((pw_zfast_kernel<Tin, PZ, RJ, 2, Epi, 512>), grid, block, 0, s, a);
-    } else {
-        if (cfg.wpb <= 4)
-            hipLaunchKernelGGL((pw_zfast_kernel<Tin, PZ, RJ, 1, Epi, 256>), grid, block, 0, s, a);
-        else
-            hipLaunchKernelGGL((pw_zfast_kernel<Tin, PZ, RJ, 1, Epi, 512>), grid, block, 0, s, a);
+void launch_k(const ZfK<Tin> &a, const TileCfg &cfg, bool pack, dim3 grid, dim3 block, hipStream_t s) {
+    if constexpr (PZ == 1) {
+        if (pack) return launch_m<Tin, PZ, RJ, Epi, 512, true>(a, cfg, grid, block, s);
     }
+    if (cfg.wpb <= 4)
+        launch_m<Tin, PZ, RJ, Epi, 256, false>(a, cfg, grid, block, s);
+    else
+        launch_m<Tin, PZ, RJ, Epi, 512, false>(a, cfg, grid, block, s);
 }
 
 template <typename Tin, int PZ, int RJ>
@@ -423,6 +456,12 @@ pw_status launch_t(const FwdArgs &g, const TileCfg &cfg, hipStream_t s) {
     a.out_si = g.out_sz;
     a.nkc = static_cast<int32_t>((g.nz + 64 * PZ - 1) / (64 * PZ));
     a.nty = static_cast<int32_t>((g.ny + RJ - 1) / RJ);
+    const int64_t packed = packed_strips(g.nz, a.nty);
+    const bool pack = PZ == 1 && packed < int64_t(a.nkc) * a.nty;
+    if (pack) {
+        a.nkc = 1;
+        a.nty = static_cast<int32_t>(packed);
+    }
     a.xlen = cfg.zlen;
     a.nxc = static_cast<int32_t>((g.nx + cfg.zlen - 1) / cfg.zlen);
     a.wpb = cfg.wpb;
@@ -435,9 +474,9 @@ pw_status launch_t(const FwdArgs &g, const TileCfg &cfg, hipStream_t s) {
     a.cw = static_cast<const Tc *>(g.cw);
     a.alpha = static_cast<Tc>(g.alpha);
     if (g.epilogue)
-        launch_k<Tin, PZ, RJ, true>(a, cfg, grid, block, s);
+        launch_k<Tin, PZ, RJ, true>(a, cfg, pack, grid, block, s);
     else
-        launch_k<Tin, PZ, RJ, false>(a, cfg, grid, block, s);
+        launch_k<Tin, PZ, RJ, false>(a, cfg, pack, grid, block, s);
     return hip_fail(hipGetLastError(), "z-fastest forward kernel launch");
 }
 
