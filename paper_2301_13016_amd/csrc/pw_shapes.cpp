@@ -13,7 +13,9 @@
 //
 // where whole rounds count one each and a partly filled round counts its
 // share, but at least 0.8: below that the wavefronts in flight no longer
-// saturate the memory and the round is as long as its latency.  `cost` is a
+// saturate the memory and the round is as long as its latency.  Marches cut
+// into as many chunks as one round holds are tried beside the fixed counts
+// (3 % over 72 grids whose pick it changed).  `cost` is a
 // shape's time per level of a full round, in arbitrary units, and shapes of
 // different widths compete through their wavefront counts: a strip that a
 // narrow grid half fills costs as much as a full one.
@@ -35,7 +37,7 @@
 namespace pw {
 
 TileCfg cheapest_shape(const ShapeCost *s, int n, int64_t lead, int64_t rows, int64_t march, double start) {
-    static const int kChunks[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 16, 24, 32, 48, 64, 128};
+    static const int kChunks[] = {0, 1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 16, 24, 32, 48, 64, 128};
     TileCfg best;
     double best_cost = -1.0;
     const int levels = static_cast<int>(march);   // extents are at most 2^30 plus the halo
@@ -43,8 +45,10 @@ TileCfg cheapest_shape(const ShapeCost *s, int n, int64_t lead, int64_t rows, in
         const int64_t blocks = (rows + s[i].ry - 1) / s[i].ry;
         double strips = static_cast<double>((lead + s[i].cols - 1) / s[i].cols) * static_cast<double>(blocks);
         if (s[i].packs) strips = std::min(strips, static_cast<double>(packed_strips(lead, blocks)));
+        const int fill = static_cast<int>(std::min(128.0, s[i].slots / strips));
         for (int c : kChunks) {
-            if (c > levels) break;
+            if (c == 0) c = fill;   // as many chunks as one round holds
+            if (c < 1 || c > levels) continue;
             const int z = (levels + c - 1) / c, chunks = (levels + z - 1) / z;
             const double q = strips * chunks / s[i].slots;
             const double whole = static_cast<double>(static_cast<int64_t>(q)), part = q - whole;
