@@ -73,7 +73,9 @@ __global__ __launch_bounds__(MaxT) void pw_forward_kernel(FwdK<Tin> a) {
 // strip_march_lds): the workgroup covers W consecutive strips in y.  Every
 // wavefront runs, also one whose strip lies past the grid, so that all reach
 // the same barriers.
-template <typename Tin, int PX, int RY, int Depth, int Epi, int Bc, int W, bool NtOwn = false>
+// Whole: every strip lies wholly inside the grid in x (nx a multiple of
+// 64 * PX), and the kernel carries no code for strips at the x end.
+template <typename Tin, int PX, int RY, int Depth, int Epi, int Bc, int W, bool NtOwn = false, bool Whole = false>
 __global__ __launch_bounds__(64 * W) void pw_forward_lds_kernel(FwdK<Tin> a) {
     __shared__ EdgeLds<Tin, PX, W> L;
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
@@ -82,7 +84,10 @@ __global__ __launch_bounds__(64 * W) void pw_forward_lds_kernel(FwdK<Tin> a) {
     const int t2 = t / a.nzc;
     const int tx = t2 % a.ntx;
     const int ty = (t2 / a.ntx) * W + wave;
-    strip_march_lds<Tin, PX, RY, Depth, Epi, Bc, W, NtOwn>(a, L, tx, ty, cz, wave);
+    if constexpr (Whole)
+        strip_march_lds_f<Tin, PX, RY, Depth, Epi, Bc, W, true, NtOwn>(a, L, tx, ty, cz, wave);
+    else
+        strip_march_lds<Tin, PX, RY, Depth, Epi, Bc, W, NtOwn>(a, L, tx, ty, cz, wave);
 }
 
 // Whether a launch's addends are the interior of u, v, w themselves (same
@@ -246,6 +251,15 @@ void launch_lds_b(const FwdK<Tin> &a, const FwdArgs &g, dim3 grid, dim3 block, h
     if constexpr (W == 4 && NtOwn && sizeof(Tin) == sizeof(typename Storage<Tin>::Tc)) {
         if (addends_are_fields<Tin>(g)) {
             hipLaunchKernelGGL((pw_forward_lds_kernel<Tin, PX, RY, 1, kEpiSelf, Bc, W, NtOwn>), grid, block, 0, s, a);
+            return;
+        }
+    }
+    if constexpr (Bc == 0 && RY == 4) {
+        // four-row strips fill the register file, and code that a grid of whole
+        // strips never runs costs it registers: 1024x1024x256 FP64 2.29 -> 2.22
+        // ms, FP16 0.94 -> 0.91, FP32 1.13 -> 1.09
+        if (!g.epilogue && g.nx % (64 * PX) == 0) {
+            hipLaunchKernelGGL((pw_forward_lds_kernel<Tin, PX, RY, 1, 0, Bc, W, NtOwn, true>), grid, block, 0, s, a);
             return;
         }
     }
