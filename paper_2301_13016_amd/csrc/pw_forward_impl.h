@@ -131,11 +131,14 @@ void launch_fwd_b(const FwdK<Tin> &a, const TileCfg &cfg, dim3 grid, dim3 block,
 template <typename Tin, int PX, int RY, int Epi>
 void launch_fwd_k(const FwdK<Tin> &a, const TileCfg &cfg, bool pack, dim3 grid, dim3 block, hipStream_t s) {
     if constexpr (PX == 1) {
-        if (pack) {   // built for one bound only
+        if (pack) {
+            // built for up to four wavefronts only: under the bound for eight,
+            // four-row FP64 strips spilled up to 284 bytes a lane: 158x229x205
+            // 134.4 us, without 83.7; with the epilogue 343 and 117
             if (cfg.depth == 2 && Epi != kEpiSelf)
-                hipLaunchKernelGGL((pw_forward_kernel<Tin, PX, RY, 2, Epi, 0, 512, true>), grid, block, 0, s, a);
+                hipLaunchKernelGGL((pw_forward_kernel<Tin, PX, RY, 2, Epi, 0, 256, true>), grid, block, 0, s, a);
             else
-                hipLaunchKernelGGL((pw_forward_kernel<Tin, PX, RY, 1, Epi, 0, 512, true>), grid, block, 0, s, a);
+                hipLaunchKernelGGL((pw_forward_kernel<Tin, PX, RY, 1, Epi, 0, 256, true>), grid, block, 0, s, a);
             return;
         }
     }
@@ -197,11 +200,12 @@ pw_status launch_fwd_t(const FwdArgs &g, const TileCfg &cfg, hipStream_t s) {
     if (pack) {
         a.ntx = 1;
         a.nty = static_cast<int32_t>(packed);
+        a.wpb = cfg.wpb > 4 ? 4 : cfg.wpb;   // strips are independent: no result changes
     }
-    const int64_t nblk_y = (a.nty + cfg.wpb - 1) / cfg.wpb;
+    const int64_t nblk_y = (a.nty + a.wpb - 1) / a.wpb;
     const int64_t nblocks = static_cast<int64_t>(a.ntx) * nblk_y * a.nzc;
     if (nblocks <= 0 || nblocks > 0x7fffffffLL) return fail(PW_ERR_UNSUPPORTED, "grid too large");
-    const dim3 grid(static_cast<unsigned>(nblocks)), block(64 * cfg.wpb);
+    const dim3 grid(static_cast<unsigned>(nblocks)), block(64 * a.wpb);
     bool self = false;
     if constexpr (sizeof(Tin) == sizeof(typename Storage<Tin>::Tc)) {
         self = cfg.wpb <= 4 && addends_are_fields<Tin>(g);

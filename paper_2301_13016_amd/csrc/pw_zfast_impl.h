@@ -421,7 +421,8 @@ void launch_m(const ZfK<Tin> &a, const TileCfg &cfg, dim3 grid, dim3 block, hipS
 template <typename Tin, int PZ, int RJ, bool Epi>
 void launch_k(const ZfK<Tin> &a, const TileCfg &cfg, bool pack, dim3 grid, dim3 block, hipStream_t s) {
     if constexpr (PZ == 1) {
-        if (pack) return launch_m<Tin, PZ, RJ, Epi, 512, true>(a, cfg, grid, block, s);
+        if (pack)   // built for up to four wavefronts only, see launch_t
+            return launch_m<Tin, PZ, RJ, Epi, 256, true>(a, cfg, grid, block, s);
     }
     if (cfg.wpb <= 4)
         launch_m<Tin, PZ, RJ, Epi, 256, false>(a, cfg, grid, block, s);
@@ -458,17 +459,20 @@ pw_status launch_t(const FwdArgs &g, const TileCfg &cfg, hipStream_t s) {
     a.nty = static_cast<int32_t>((g.ny + RJ - 1) / RJ);
     const int64_t packed = packed_strips(g.nz, a.nty);
     const bool pack = PZ == 1 && packed < int64_t(a.nkc) * a.nty;
-    if (pack) {
-        a.nkc = 1;
-        a.nty = static_cast<int32_t>(packed);
-    }
     a.xlen = cfg.zlen;
     a.nxc = static_cast<int32_t>((g.nx + cfg.zlen - 1) / cfg.zlen);
     a.wpb = cfg.wpb;
-    const int64_t nblk_y = (a.nty + cfg.wpb - 1) / cfg.wpb;
+    if (pack) {
+        a.nkc = 1;
+        a.nty = static_cast<int32_t>(packed);
+        // the bound for eight wavefronts spills strips of four rows; strips
+        // are independent, so smaller workgroups change no result
+        if (a.wpb > 4) a.wpb = 4;
+    }
+    const int64_t nblk_y = (a.nty + a.wpb - 1) / a.wpb;
     const int64_t nblocks = static_cast<int64_t>(a.nkc) * nblk_y * a.nxc;
     if (nblocks <= 0 || nblocks > 0x7fffffffLL) return fail(PW_ERR_UNSUPPORTED, "grid too large");
-    const dim3 grid(static_cast<unsigned>(nblocks)), block(64 * cfg.wpb);
+    const dim3 grid(static_cast<unsigned>(nblocks)), block(64 * a.wpb);
     a.cu = static_cast<const Tc *>(g.cu);
     a.cv = static_cast<const Tc *>(g.cv);
     a.cw = static_cast<const Tc *>(g.cw);
