@@ -670,8 +670,9 @@ TileCfg default_adjoint_tile(const AdjArgs &a, pw_dtype dt) {
     // wavefronts" of two rows (FP64: one): 32x32x64 9.6 -> 5.7 us,
     // 250x250x100 68.8 -> 62.3 and FP64 139 -> 117, 42x587x244 77 -> 60.
     (void)dt;
-    static const ShapeCost s[] = {{1, 2, 1, 1, 0, kWaveCols, 1024, 1.0}, {1, 4, 1, 1, 0, kWaveCols, 1024, 1.6}};
-    return cheapest_shape(s, 2, a.nx + 2 * a.h, a.ny + 2 * a.h, a.nz + 2 * a.h, 2.5);
+    static const ShapeCost s[] = {{1, 2, 1, 1, 0, kWaveCols, 1024, 1.0, 2.5},
+                                  {1, 4, 1, 1, 0, kWaveCols, 1024, 1.6, 2.5}};
+    return cheapest_shape(s, 2, a.nx + 2 * a.h, a.ny + 2 * a.h, a.nz + 2 * a.h, false);
 }
 
 TileCfg coeff_grad_tile(const pw_grid &g, pw_dtype dt) {
@@ -682,10 +683,11 @@ TileCfg coeff_grad_tile(const pw_grid &g, pw_dtype dt) {
     // Against four rows (FP64: one) in one round of 2048 wavefronts and at
     // least eight levels, with the wind gradients: 32x32x64 23.2 -> 12.8 us,
     // 512x512x32 109.5 -> 103, FP64 250x250x100 172 -> 130.
-    static const ShapeCost f32[] = {{1, 4, 1, 1, 0, kWaveCols, 2048, 1.0}};
-    static const ShapeCost f64[] = {{1, 2, 1, 1, 0, kWaveCols, 1024, 1.0}, {1, 4, 1, 1, 0, kWaveCols, 1024, 1.6}};
+    static const ShapeCost f32[] = {{1, 4, 1, 1, 0, kWaveCols, 2048, 1.0, 2.5}};
+    static const ShapeCost f64[] = {{1, 2, 1, 1, 0, kWaveCols, 1024, 1.0, 2.5},
+                                    {1, 4, 1, 1, 0, kWaveCols, 1024, 1.6, 2.5}};
     return cheapest_shape(dt == PW_F64 ? f64 : f32, dt == PW_F64 ? 2 : 1, g.nx + 2 * g.halo, g.ny + 2 * g.halo,
-                          g.nz + 2 * g.halo, 2.5);
+                          g.nz + 2 * g.halo, false);
 }
 
 int64_t adjoint_strips(const pw_grid &g, int ry) {

@@ -370,16 +370,16 @@ pw_status advect_general(const pw_grid *grid, const pw_layout *layout, pw_dtype 
                     "unsupported forward tile cols=%d rows=%d zlen=%d waves=%d prefetch=%d share_rows=%d",
                     tile->cols_per_lane, tile->rows_per_strip, tile->zlen, tile->waves_per_group, tile->prefetch,
                     tile->share_rows);
-    TileCfg cfg;
-    const char *how = "given";
-    PW_TRY(forward_shape(grid, a, in_dtype, tile, &cfg, &how));
-    if (bc) {
+    if (bc) {   // before the shape, which depends on them
         int32_t addr[3];
         PW_TRY(boundary_rules(grid, bc, addr, &a.bcv));
         a.bcx = addr[0];
         a.bcy = addr[1];
         a.bcz = addr[2];
     }
+    TileCfg cfg;
+    const char *how = "given";
+    PW_TRY(forward_shape(grid, a, in_dtype, tile, &cfg, &how));
     int dev = 0;
     if (ep) {
         // the addends: output layout, compute type; each either is its output

@@ -136,43 +136,63 @@ bool tile_supported(const TileCfg &c, pw_dtype dt) {
 }
 
 TileCfg default_forward_tile(const FwdArgs &a, pw_dtype dt) {
-    // Narrow and ragged grids: one column per lane, counted as packed strips
-    // (see strip_march_t) in FP32 and 16-bit storage: against the shapes that
-    // plain strips made cheapest FP32 267x185x66 31.3 -> 25.3 us, 337x713x26
-    // 46.4 -> 40.4, BF16 78x230x187 29.8 -> 23.1 (FP64's two-column strips hold
-    // their own: 66x200x200 27.6 us, packed 37).  Wide ones: 16 bytes per lane
-    // with shared rows -- a short workgroup (two wavefronts of one row, FP32)
-    // while the grid is small enough that wavefronts in flight decide, tall
-    // ones (four wavefronts of two rows, half the rows read twice) where the
-    // bytes do.  Measured, tall against short: 512x512x64 (aligned rows) 69.4 /
-    // 82.6 us, 415x420x169 155 / 177, 1000x300x64 106 / 117, but 96.5 / 98.6 at
-    // 536x186x162 and 34.7 / 35.4 at 250x250x100; FP64 250x250x100 63 / 69,
-    // 201x143x117 46 / 42.
+    // Narrow and ragged grids: one column per lane, packed where that makes
+    // fewer strips (see strip_march_t): against the shapes that plain strips
+    // made cheapest FP32 267x185x66 31.3 -> 25.3 us, 337x713x26 46.4 -> 40.4,
+    // BF16 78x230x187 29.8 -> 23.1.  Wide ones: 16 bytes per lane with shared
+    // rows -- a short workgroup (two wavefronts of one row, FP32) while the grid
+    // is small enough that wavefronts in flight decide, tall ones (four
+    // wavefronts of two rows, half the rows read twice) where the bytes do.
     const int64_t pts = a.nx * a.ny * a.nz;
+    const bool rules = has_rules(a);
+    const auto pick = [&](const ShapeCost *s, int n) { return cheapest_shape(s, n, a.nx, a.ny, a.nz, !rules); };
+    if (rules) {
+        // One-column strips are not packed here, and strips at the x end cost
+        // more (bc_patch_x; tall shared workgroups FP32 600x600x120 404 us, of
+        // one row 281): lists of their own, fitted to 141 grids in FP32, 125 in
+        // FP64 and 111 in BF16, 4, 4 and 5 % slower than the best shape.  The
+        // lists below, whose packed strips do not run here, were 13, 9 and 18 %
+        // slower: FP32 134x95x92 20.8 -> 17.8 us, 140x300x150 66.5 -> 53.9,
+        // BF16 401x134x71 51.2 -> 32.0, FP64 136x767x21 53.1 -> 41.9.
+        static const ShapeCost f32[] = {{1, 2, 1, 1, 0, 64, 2048, 1.00, 0.3}, {1, 4, 1, 1, 0, 64, 2048, 1.34, 3.3},
+                                        {2, 2, 1, 1, 0, 128, 2048, 1.41, 0.5, 1.37},
+                                        {4, 1, 1, 1, 0, 256, 2048, 1.40, 0.3, 1.12},
+                                        {4, 1, 4, 1, 2, 256, 2048, 1.27, 1.7, 1.13},
+                                        {4, 2, 4, 1, 2, 256, 1024, 1.15, 3.1, 2.35}};
+        static const ShapeCost f64[] = {{1, 2, 1, 1, 0, 64, 2048, 1.00, 0.3}, {1, 4, 1, 1, 0, 64, 1024, 0.69, 5.0},
+                                        {2, 2, 1, 1, 0, 128, 1024, 0.80, 1.0, 1.04},
+                                        {2, 2, 4, 1, 2, 128, 1024, 0.65, 5.0, 1.82}};
+        static const ShapeCost half[] = {{1, 2, 1, 1, 0, 64, 2048, 1.00, 0.3}, {1, 4, 1, 1, 0, 64, 2048, 1.67, 1.3},
+                                         {2, 2, 1, 1, 0, 128, 2048, 1.66, 0.3}, {2, 4, 1, 1, 0, 128, 2048, 3.06, 1.0}};
+        return dt == PW_F32 ? pick(f32, 6) : dt == PW_F64 ? pick(f64, 4) : pick(half, 4);
+    }
     if (dt == PW_F32) {
-        static const ShapeCost small[] = {{1, 2, 1, 1, 0, 64, 2048, 0.90, true}, {1, 4, 1, 1, 0, 64, 2048, 1.50, true},
+        static const ShapeCost small[] = {{1, 2, 1, 1, 0, 64, 2048, 0.90}, {1, 4, 1, 1, 0, 64, 2048, 1.50},
                                           {4, 1, 2, 1, 2, 256, 2048, 0.95}};
         static const ShapeCost large[] = {{1, 4, 1, 1, 0, 64, 2048, 1.50}, {4, 2, 4, 1, 2, 256, 1024, 1.35}};
-        return pts < 16000000 ? cheapest_shape(small, 3, a.nx, a.ny, a.nz)
-                              : cheapest_shape(large, 2, a.nx, a.ny, a.nz);
+        return pts < 16000000 ? pick(small, 3) : pick(large, 2);
     }
     if (dt == PW_F64) {
-        static const ShapeCost small[] = {{1, 2, 1, 1, 0, 64, 1024, 0.82}, {2, 1, 1, 1, 0, 128, 1024, 0.59},
-                                          {2, 2, 1, 1, 0, 128, 1024, 1.05}};
+        // Two lists: a tall shape with too few wavefronts to fill the chip loses
+        // (306x492x21, 3.2 M points: 44.8 us, one-row strips 33.9), and where they
+        // do the others read more (250x250x100, 6.2 M: 65.3 us, two-row strips
+        // 72.2); around 5 M points they are even (208x631x30 51.5 / 49.7,
+        // 207x278x87 62.2 / 67.7).  84 grids below, 4 % slower than the best
+        // shape (with one-column strips counted as plain ones 6 %), 53 above, 2 %.
+        static const ShapeCost small[] = {{1, 2, 1, 1, 0, 64, 1024, 1.00, 0.5}, {2, 1, 1, 1, 0, 128, 1024, 0.55, 0.9},
+                                          {2, 2, 1, 1, 0, 128, 1024, 0.93, 1.4}};
         static const ShapeCost large[] = {{1, 4, 1, 1, 0, 64, 1024, 1.30}, {2, 2, 4, 1, 2, 128, 1024, 1.00}};
-        return pts < 5000000 ? cheapest_shape(small, 3, a.nx, a.ny, a.nz)
-                             : cheapest_shape(large, 2, a.nx, a.ny, a.nz);
+        return pts < 5000000 ? pick(small, 3) : pick(large, 2);
     }
-    static const ShapeCost small[] = {{1, 2, 1, 1, 0, 64, 2048, 0.67, true}, {1, 4, 1, 1, 0, 64, 2048, 1.09, true},
+    static const ShapeCost small[] = {{1, 2, 1, 1, 0, 64, 2048, 0.67}, {1, 4, 1, 1, 0, 64, 2048, 1.09},
                                       {2, 2, 1, 1, 0, 128, 2048, 0.97}, {4, 2, 2, 1, 1, 256, 2048, 1.58}};
     static const ShapeCost large[] = {{1, 4, 1, 1, 0, 64, 2048, 1.09}, {4, 4, 2, 1, 2, 256, 1024, 2.00}};
-    return pts < 64000000 ? cheapest_shape(small, 4, a.nx, a.ny, a.nz)
-                          : cheapest_shape(large, 2, a.nx, a.ny, a.nz);
+    return pts < 64000000 ? pick(small, 4) : pick(large, 2);
 }
 
 pw_status launch_forward(const FwdArgs &a, pw_dtype dt, const TileCfg &cfg, hipStream_t s) {
     if (!tile_supported(cfg, dt)) return fail(PW_ERR_INVALID_ARG, "unsupported tile configuration");
-    const bool bc = a.bcx != PW_HALO_KEEP || a.bcy != PW_HALO_KEEP || a.bcz != PW_HALO_KEEP || a.bcv != 0;
+    const bool bc = has_rules(a);
     if (bc && cfg.share == 0 && cfg.wpb > 4) {
         // boundary rules are built for up to four wavefronts per workgroup;
         // the strips are independent, so regrouping them changes no result

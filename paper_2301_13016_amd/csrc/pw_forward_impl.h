@@ -193,13 +193,11 @@ FwdK<Tin> make_fwdk(const FwdArgs &g, const TileCfg &cfg) {
 template <typename Tin, int PX, int RY>
 pw_status launch_fwd_t(const FwdArgs &g, const TileCfg &cfg, hipStream_t s) {
     FwdK<Tin> a = make_fwdk<Tin, PX, RY>(g, cfg);
-    // packed strips where they are fewer (see strip_march_t)
-    const int64_t packed = packed_strips(g.nx, a.nty);
-    const bool pack = PX == 1 && packed < int64_t(a.ntx) * a.nty && g.bcv == 0 && g.bcx == PW_HALO_KEEP &&
-                      g.bcy == PW_HALO_KEEP && g.bcz == PW_HALO_KEEP;
+    const Strips st = strips_of(g.nx, g.ny, 64 * PX, RY, !has_rules(g));
+    const bool pack = st.packed;
     if (pack) {
         a.ntx = 1;
-        a.nty = static_cast<int32_t>(packed);
+        a.nty = static_cast<int32_t>(st.count);
         a.wpb = cfg.wpb > 4 ? 4 : cfg.wpb;   // strips are independent: no result changes
     }
     const int64_t nblk_y = (a.nty + a.wpb - 1) / a.wpb;

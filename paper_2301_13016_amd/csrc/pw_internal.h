@@ -102,20 +102,39 @@ constexpr int kWaveCols = 62;
 
 // A launch shape the rule of pw_shapes.cpp may pick: its tile (without the
 // march length), the columns of one of its strips, the wavefronts of it that
-// the chip holds at once, and its time per level of a full round.
+// the chip holds at once, its time per level of a full round, the start of its
+// pipeline in levels, and the weight of a strip at the grid's x end that the
+// grid does not fill, against a full one.
 struct ShapeCost {
     int px, ry, wpb, depth, share;
     int cols;
     int slots;
     double cost;
-    bool packs = false;   // packed strips where they are fewer (see packed_strips)
+    double start = 1.5;
+    double ragged = 1.0;
 };
-// Strips of a grid whose blocks of rows are packed into wavefronts end to end,
-// each block n + 2 positions long (see strip_march_t and pw_zfast_impl.h).
-inline int64_t packed_strips(int64_t n, int64_t blocks) { return (blocks * (n + 2) - 1 + kWaveCols - 1) / kWaveCols; }
+// The strips that cover `lead` elements along the lanes and `rows` rows, in
+// strips of cols x ry.  Strips of one-column lanes (64 columns) may be packed:
+// the row blocks are laid end to end, each lead + 2 positions long, and cut
+// into pieces of 62 (see strip_march_t and pw_zfast_impl.h); they are where
+// that makes fewer.  The launches and the rule both count with this function,
+// so that the rule weighs the strips that run.
+struct Strips {
+    int64_t count;
+    bool packed;
+};
+inline Strips strips_of(int64_t lead, int64_t rows, int cols, int ry, bool may_pack) {
+    const int64_t blocks = (rows + ry - 1) / ry, plain = (lead + cols - 1) / cols * blocks;
+    const int64_t packed = (blocks * (lead + 2) - 1 + kWaveCols - 1) / kWaveCols;
+    return may_pack && cols == 64 && packed < plain ? Strips{packed, true} : Strips{plain, false};
+}
+// Whether a launch reads through boundary rules (which are not built packed).
+inline bool has_rules(const FwdArgs &a) {
+    return a.bcx != PW_HALO_KEEP || a.bcy != PW_HALO_KEEP || a.bcz != PW_HALO_KEEP || a.bcv != 0;
+}
 // The cheapest of n shapes, march length included, for a grid of `lead`
 // elements along the lanes, `rows` rows and `march` levels.
-TileCfg cheapest_shape(const ShapeCost *s, int n, int64_t lead, int64_t rows, int64_t march, double start = 1.5);
+TileCfg cheapest_shape(const ShapeCost *s, int n, int64_t lead, int64_t rows, int64_t march, bool may_pack);
 
 bool tile_supported(const TileCfg &c, pw_dtype dt);
 bool adjoint_tile_supported(const TileCfg &c);

@@ -36,15 +36,17 @@
 
 namespace pw {
 
-TileCfg cheapest_shape(const ShapeCost *s, int n, int64_t lead, int64_t rows, int64_t march, double start) {
+TileCfg cheapest_shape(const ShapeCost *s, int n, int64_t lead, int64_t rows, int64_t march, bool may_pack) {
     static const int kChunks[] = {0, 1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 16, 24, 32, 48, 64, 128};
     TileCfg best;
     double best_cost = -1.0;
-    const int levels = static_cast<int>(march);   // extents are at most 2^30 plus the halo
+    const int levels = static_cast<int>(std::min<int64_t>(march, INT32_MAX));
     for (int i = 0; i < n; ++i) {
-        const int64_t blocks = (rows + s[i].ry - 1) / s[i].ry;
-        double strips = static_cast<double>((lead + s[i].cols - 1) / s[i].cols) * static_cast<double>(blocks);
-        if (s[i].packs) strips = std::min(strips, static_cast<double>(packed_strips(lead, blocks)));
+        const Strips st = strips_of(lead, rows, s[i].cols, s[i].ry, may_pack);
+        const double strips = static_cast<double>(st.count);
+        const double level = lead % s[i].cols == 0 || st.packed   // the strips at the x end weigh more
+                                 ? s[i].cost
+                                 : s[i].cost * (1.0 + (s[i].ragged - 1.0) / static_cast<double>((lead + s[i].cols - 1) / s[i].cols));
         const int fill = static_cast<int>(std::min(128.0, s[i].slots / strips));
         for (int c : kChunks) {
             if (c == 0) c = fill;   // as many chunks as one round holds
@@ -53,7 +55,7 @@ TileCfg cheapest_shape(const ShapeCost *s, int n, int64_t lead, int64_t rows, in
             const double q = strips * chunks / s[i].slots;
             const double whole = static_cast<double>(static_cast<int64_t>(q)), part = q - whole;
             const double rounds = whole + (part > 0.0 ? (part > 0.8 ? part : 0.8) : 0.0);
-            const double cost = s[i].cost * rounds * (z + start);
+            const double cost = level * rounds * (z + s[i].start);
             if (best_cost < 0.0 || cost < best_cost) {
                 best_cost = cost;
                 best = TileCfg{s[i].px, s[i].ry, z, s[i].wpb, s[i].depth, s[i].share};

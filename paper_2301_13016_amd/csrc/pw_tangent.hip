@@ -365,10 +365,10 @@ TileCfg default_tangent_tile(const TanArgs &a, pw_dtype dt) {
     // two-row strips; FP32: of two columns per lane where the grid fills them
     if (dt == PW_F64) {
         static const ShapeCost s[] = {{1, 1, 1, 1, 0, 64, 1024, 0.885}, {1, 2, 1, 1, 0, 64, 1024, 1.55}};
-        return cheapest_shape(s, 2, a.f.nx, a.f.ny, a.f.nz);
+        return cheapest_shape(s, 2, a.f.nx, a.f.ny, a.f.nz, false);
     }
     static const ShapeCost s[] = {{1, 2, 1, 1, 0, 64, 1024, 0.95}, {2, 2, 1, 1, 0, 128, 1024, 1.57}};
-    return cheapest_shape(s, 2, a.f.nx, a.f.ny, a.f.nz);
+    return cheapest_shape(s, 2, a.f.nx, a.f.ny, a.f.nz, false);
 }
 
 pw_status launch_tangent(const TanArgs &a, pw_dtype dt, const TileCfg &cfg, hipStream_t s) {

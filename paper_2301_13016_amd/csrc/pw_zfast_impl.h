@@ -37,15 +37,6 @@ namespace zf {
 
 using namespace dev;
 
-// Packed strips (one level per lane, Pack): the row blocks of RJ rows are laid
-// end to end, each with the level below and the level above its column, and
-// cut into pieces of 62 positions; a wavefront loads the 64 positions around
-// its piece, so the lanes' neighbours are theirs in the column too, and every
-// row is read at its lane's own offset.  A column that fills few of a strip's
-// 64 levels (75 of 128, 20 of 64) then leaves no lanes idle but the halo's two
-// and the piece's two.  Taken where that makes fewer strips (packed_strips).
-// FP32, best shapes: 300x300x75 66.3 -> 46.4 us, 500x300x20 23.5 -> 16.6,
-// 512x512x66 157 -> 112; with the epilogue 75.6 -> 60.9, 44.2 -> 27.2, 174 -> 151.
 template <typename Tin> struct ZfK {
     using Tc = typename Storage<Tin>::Tc;
     const Tin *u, *v, *w;
@@ -261,9 +252,19 @@ __device__ __forceinline__ void column(const ZPlane<Tin, PZ, RJ> &m, const ZPlan
 
 // One work item: level chunk tk (64*PZ levels), y-strip ty (RJ rows), marched
 // through x-chunk cx.  All 64 lanes must be active.  Full: the level chunk
-// lies wholly inside the grid ((tk+1)*64*PZ <= nz), so every lane loads
-// owns PZ outputs; otherwise vectors may run past the column's end (see load_row)
-// and each lane stores only its levels inside the grid.
+// lies wholly inside the grid ((tk+1)*64*PZ <= nz), so every lane owns PZ
+// outputs; otherwise vectors may run past the column's end (see load_row) and
+// each lane stores only its levels inside the grid.
+//
+// Packed strips (one level per lane, Pack): the row blocks of RJ rows are laid
+// end to end, each with the level below and the level above its column, and
+// cut into pieces of 62 positions; a wavefront loads the 64 positions around
+// its piece, so the lanes' neighbours are theirs in the column too, and every
+// row is read at its lane's own offset.  A column that fills few of a strip's
+// 64 levels (75 of 128, 20 of 64) then leaves no lanes idle but the halo's two
+// and the piece's two.  Taken where that makes fewer strips (strips_of).
+// FP32, best shapes: 300x300x75 66.3 -> 46.4 us, 500x300x20 23.5 -> 16.6,
+// 512x512x66 157 -> 112; with the epilogue 75.6 -> 60.9, 44.2 -> 27.2, 174 -> 151.
 template <typename Tin, int PZ, int RJ, bool Full, int Depth, bool Epi, bool Pack>
 __device__ __forceinline__ void xmarch(const ZfK<Tin> &a, int tk, int ty, int cx) {
     using Tc = typename Storage<Tin>::Tc;
@@ -457,14 +458,14 @@ pw_status launch_t(const FwdArgs &g, const TileCfg &cfg, hipStream_t s) {
     a.out_si = g.out_sz;
     a.nkc = static_cast<int32_t>((g.nz + 64 * PZ - 1) / (64 * PZ));
     a.nty = static_cast<int32_t>((g.ny + RJ - 1) / RJ);
-    const int64_t packed = packed_strips(g.nz, a.nty);
-    const bool pack = PZ == 1 && packed < int64_t(a.nkc) * a.nty;
+    const Strips st = strips_of(g.nz, g.ny, 64 * PZ, RJ, true);
+    const bool pack = st.packed;
     a.xlen = cfg.zlen;
     a.nxc = static_cast<int32_t>((g.nx + cfg.zlen - 1) / cfg.zlen);
     a.wpb = cfg.wpb;
     if (pack) {
         a.nkc = 1;
-        a.nty = static_cast<int32_t>(packed);
+        a.nty = static_cast<int32_t>(st.count);
         // the bound for eight wavefronts spills strips of four rows; strips
         // are independent, so smaller workgroups change no result
         if (a.wpb > 4) a.wpb = 4;
