@@ -32,6 +32,9 @@
 #include "pw_stencil.h"
 
 namespace pw {
+
+std::vector<TileCfg> batch_candidates(const TileCfg &start);
+
 namespace {
 
 using namespace dev;
@@ -49,15 +52,16 @@ __global__ void batch_reset_kernel(unsigned long long *counter) {
     if (threadIdx.x < kXcds) counter[threadIdx.x * kCtrStride] = 0ull;
 }
 
-// Depth: planes in flight (1 or 2).  MaxT: workgroup size bound (built for
-// 256 and 512 threads, as the single-grid kernels).  PX 0: each subdomain's
-// strips have the width its work-list entry names (1, 2 or 4 columns per lane;
-// the choice is wave-uniform, made per work item), four-column ones two rows
-// where the tile says four.
 // Rows of a strip of px columns per lane where the tile says ry and leaves the
 // columns to the subdomain (four columns hold two rows in registers).
 __host__ __device__ constexpr int sub_rows(int px, int ry) { return px == 4 && ry > 2 ? 2 : ry; }
 
+// Depth: planes in flight (1 or 2).  MaxT: workgroup size bound (built for
+// 256 and 512 threads, as the single-grid kernels).  PX 0: each subdomain's
+// strips have the width its work-list entry names (1, 2 or 4 columns per lane;
+// the choice is wave-uniform, made per work item), four-column ones two rows
+// where the tile says four.  At most four columns per lane: the narrowest
+// padded row, three elements, then holds the PX - 1 that load_row needs.
 template <typename Tin, int PX, int RY, int Depth, int MaxT>
 __global__ __launch_bounds__(MaxT) void pw_batch_kernel(const BatchSub<Tin> *__restrict__ subs, int nsub,
                                                        int64_t nitems, unsigned long long *counter) {
@@ -288,6 +292,22 @@ bool batch_tile_ok(const TileCfg &c) {
 
 }  // namespace
 
+// The shapes pw_batch_tune times: the one the batch has, then the others.
+std::vector<TileCfg> pw::batch_candidates(const TileCfg &start) {
+    std::vector<TileCfg> out{start};
+    for (int px : {0, 1, 2, 4})
+        for (int ry : {1, 2, 4})
+            for (int zl : {16, 32, 64, 128, 256})
+                for (int wpb : {1, 4})
+                    for (int depth : {1, 2}) {
+                        const TileCfg c{px, ry, zl, wpb, depth, 0};
+                        const bool same = px == start.px && ry == start.ry && zl == start.zlen && wpb == start.wpb &&
+                                          depth == start.depth;
+                        if (!same && batch_tile_ok(c)) out.push_back(c);
+                    }
+    return out;
+}
+
 extern "C" {
 
 pw_status pw_batch_create(const pw_batch_item *items, int32_t n, pw_dtype dtype, const pw_tile *tile,
@@ -460,30 +480,21 @@ pw_status pw_batch_tune(pw_batch *b, void *hip_stream, pw_tile *chosen) {
     TileCfg best = start;
     std::vector<std::pair<float, TileCfg>> t;
     pw_status st = PW_OK;
-    for (int px : {0, 1, 2, 4})
-        for (int ry : {1, 2, 4})
-            for (int zl : {32, 64, 128, 256})
-                for (int wpb : {1, 4})
-                    for (int depth : {1, 2}) {
-                            if (st != PW_OK) break;
-                            TileCfg c;
-                            c.px = px;
-                            c.ry = ry;
-                            c.zlen = zl;
-                            c.wpb = wpb;
-                            c.depth = depth;
-                            if (!batch_tile_ok(c)) continue;
-                            float ms = -1.f;
-                            st = time_tile(c, 3, &ms);
-                            if (st == PW_OK && ms > 0.f) t.emplace_back(ms, c);
-                        }
-    // the three fastest again over more runs (less sensitive to noise)
+    for (const TileCfg &c : batch_candidates(start)) {
+        float ms = -1.f;
+        st = time_tile(c, 3, &ms);
+        if (st != PW_OK) break;
+        if (ms > 0.f) t.emplace_back(ms, c);
+    }
+    // the three fastest again over more runs (less sensitive to noise), and
+    // the tile that the batch came with (the first candidate): tuning must not
+    // leave it slower
     if (st == PW_OK && !t.empty()) {
-        std::sort(t.begin(), t.end(), [](const std::pair<float, TileCfg> &x, const std::pair<float, TileCfg> &y) {
+        std::sort(t.begin() + 1, t.end(), [](const std::pair<float, TileCfg> &x, const std::pair<float, TileCfg> &y) {
             return x.first < y.first;
         });
         float best_ms = -1.f;
-        for (size_t r = 0; r < t.size() && r < 3 && st == PW_OK; ++r) {
+        for (size_t r = 0; r < t.size() && r < 4 && st == PW_OK; ++r) {
             float ms = -1.f;
             st = time_tile(t[r].second, 10, &ms);
             if (st == PW_OK && ms > 0.f && (best_ms < 0.f || ms < best_ms)) {

@@ -1,5 +1,7 @@
 // Host functions of the library that its interface does not show, for tests
 // (built by hooks.py against the built library).
+#include <vector>
+
 #include "pw_internal.h"
 
 // The strip count that the launch rule and the launches share.
@@ -30,4 +32,19 @@ extern "C" void pick(int zfast, int dtype, int64_t nx, int64_t ny, int64_t nz, i
     const pw::TileCfg c = zfast ? pw::default_zfast_tile(a, dt) : pw::default_forward_tile(a, dt);
     const int v[6] = {c.px, c.ry, c.zlen, c.wpb, c.depth, c.share};
     for (int i = 0; i < 6; ++i) out[i] = v[i];
+}
+
+// The shapes that tuning a batch times, the batch's own first.
+namespace pw {
+std::vector<TileCfg> batch_candidates(const TileCfg &start);
+}
+extern "C" int batch_candidates(const int32_t start[6], int32_t (*out)[6], int most) {
+    int n = 0;
+    for (const pw::TileCfg &c : pw::batch_candidates({start[0], start[1], start[2], start[3], start[4], start[5]})) {
+        if (n == most) break;
+        const int32_t v[6] = {c.px, c.ry, c.zlen, c.wpb, c.depth, c.share};
+        for (int i = 0; i < 6; ++i) out[n][i] = v[i];
+        ++n;
+    }
+    return n;
 }
