@@ -117,9 +117,11 @@ TileCfg entry_to_cfg(const Entry &e, int64_t zextent) {
     return c;
 }
 
-// Timing helper: mean milliseconds of `reps` launches after one warm-up;
-// launch(i) runs on buffer set i (the caller rotates its sets, so that
-// repeats do not come out of the 256 MB MALL).
+// Timing helper: mean milliseconds of `reps` launches, as a graph that is
+// replayed once before; launch(i) runs on buffer set i (the caller rotates its
+// sets, so that repeats do not come out of the 256 MB MALL).  Launched one by
+// one, kernels shorter than the host's time per launch all look alike: at
+// 32x32x64 that kept a shape of 4.2 us where the untuned one takes 2.5.
 template <typename F> float time_ms(F launch, hipStream_t s, int reps, pw_status *st) {
     hipEvent_t a, b;
     if (hipEventCreate(&a) != hipSuccess) return -1.f;
@@ -127,16 +129,23 @@ template <typename F> float time_ms(F launch, hipStream_t s, int reps, pw_status
         (void)hipEventDestroy(a);
         return -1.f;
     }
-    *st = launch(reps);
     float ms = -1.f;
-    if (*st == PW_OK && hipEventRecord(a, s) == hipSuccess) {
+    hipGraph_t g = nullptr;
+    hipGraphExec_t x = nullptr;
+    *st = PW_OK;
+    if (hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal) == hipSuccess) {
         for (int i = 0; i < reps && *st == PW_OK; ++i) *st = launch(i);
-        if (*st == PW_OK && hipEventRecord(b, s) == hipSuccess && hipEventSynchronize(b) == hipSuccess &&
-            hipEventElapsedTime(&ms, a, b) == hipSuccess)
+        const hipError_t e = hipStreamEndCapture(s, &g);
+        if (*st == PW_OK && e == hipSuccess && hipGraphInstantiate(&x, g, nullptr, nullptr, 0) == hipSuccess &&
+            hipGraphLaunch(x, s) == hipSuccess && hipEventRecord(a, s) == hipSuccess &&
+            hipGraphLaunch(x, s) == hipSuccess && hipEventRecord(b, s) == hipSuccess &&
+            hipEventSynchronize(b) == hipSuccess && hipEventElapsedTime(&ms, a, b) == hipSuccess)
             ms /= reps;
         else
             ms = -1.f;
     }
+    if (x) (void)hipGraphExecDestroy(x);
+    if (g) (void)hipGraphDestroy(g);
     (void)hipEventDestroy(a);
     (void)hipEventDestroy(b);
     return ms;
@@ -149,9 +158,12 @@ template <typename F> float time_ms(F launch, hipStream_t s, int reps, pw_status
 // Interleaving spreads slow drifts of the clock over all finalists, and the
 // median drops a round that one disturbance slowed.  (A single pass of 30
 // launches over five finalists had ranked shapes 1.8 % and 3.7 % apart the
-// wrong way round.)
+// wrong way round.)  *best is the shape that untuned calls take, a candidate
+// like the others: tuning must not leave a grid slower (32x32x64, whose march
+// the rule cuts into single levels, shorter than any candidate below).
 template <typename F>
-pw_status pick_fastest(const std::vector<TileCfg> &cands, F launch, hipStream_t s, TileCfg *best) {
+pw_status pick_fastest(std::vector<TileCfg> cands, F launch, hipStream_t s, TileCfg *best) {
+    cands.insert(cands.begin(), *best);
     std::vector<std::pair<float, size_t>> t;
     if (!cands.empty()) {
         pw_status ls = PW_OK;
