@@ -167,10 +167,14 @@ TileCfg default_forward_tile(const FwdArgs &a, pw_dtype dt) {
         return dt == PW_F32 ? pick(f32, 6) : dt == PW_F64 ? pick(f64, 4) : pick(half, 4);
     }
     if (dt == PW_F32) {
-        static const ShapeCost small[] = {{1, 2, 1, 1, 0, 64, 2048, 0.90}, {1, 4, 1, 1, 0, 64, 2048, 1.50},
-                                          {4, 1, 2, 1, 2, 256, 2048, 0.95}};
-        static const ShapeCost large[] = {{1, 4, 1, 1, 0, 64, 2048, 1.50}, {4, 2, 4, 1, 2, 256, 1024, 1.35}};
-        return pts < 16000000 ? pick(small, 3) : pick(large, 2);
+        // 137 grids, 6 % slower than the best shape.  With a line at 16 M points
+        // between the short and the tall shape, instead of the tall one's longer
+        // start, 9 %: 512x512x60 81 us, tall 68; 500x500x63 88 / 79; 400x400x99
+        // 104 / 94; 600x600x120 308 / 231.
+        static const ShapeCost s[] = {{1, 2, 1, 1, 0, 64, 2048, 0.90}, {1, 4, 1, 1, 0, 64, 2048, 1.50},
+                                      {4, 1, 2, 1, 2, 256, 2048, 0.95},
+                                      {4, 2, 4, 1, 2, 256, 1024, 0.77, 4.8, 1.21}};
+        return pick(s, 4);
     }
     if (dt == PW_F64) {
         // Two lists: a tall shape with too few wavefronts to fill the chip loses
@@ -184,10 +188,13 @@ TileCfg default_forward_tile(const FwdArgs &a, pw_dtype dt) {
         static const ShapeCost large[] = {{1, 4, 1, 1, 0, 64, 1024, 1.30}, {2, 2, 4, 1, 2, 128, 1024, 1.00}};
         return pts < 5000000 ? pick(small, 3) : pick(large, 2);
     }
-    static const ShapeCost small[] = {{1, 2, 1, 1, 0, 64, 2048, 0.67}, {1, 4, 1, 1, 0, 64, 2048, 1.09},
-                                      {2, 2, 1, 1, 0, 128, 2048, 0.97}, {4, 2, 2, 1, 1, 256, 2048, 1.58}};
-    static const ShapeCost large[] = {{1, 4, 1, 1, 0, 64, 2048, 1.09}, {4, 4, 2, 1, 2, 256, 1024, 2.00}};
-    return pts < 64000000 ? pick(small, 4) : pick(large, 2);
+    // 16-bit storage: 165 grids, 7 % slower than the best shape.  The tallest
+    // shape only where it fills its strips: BF16 512x512x60 64.6 us, two-row
+    // strips 74.3; 900x700x100 308 / 322; 600x600x120 226 / 224.
+    static const ShapeCost s[] = {{1, 2, 1, 1, 0, 64, 2048, 0.67}, {1, 4, 1, 1, 0, 64, 2048, 1.09},
+                                  {2, 2, 1, 1, 0, 128, 2048, 0.97}, {4, 2, 2, 1, 1, 256, 2048, 1.58},
+                                  {4, 4, 2, 1, 2, 256, 1024, 1.28, 4.8, 1.79}};
+    return pick(s, 5);
 }
 
 pw_status launch_forward(const FwdArgs &a, pw_dtype dt, const TileCfg &cfg, hipStream_t s) {
