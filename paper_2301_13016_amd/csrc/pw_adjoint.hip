@@ -39,8 +39,8 @@
 // no faster than the kernel (256x256x128 FP32: 75 us), without the stores 44
 // us; half the lines of a 62-column piece are shared with the next strip.
 // Strips next to each other in x therefore run on one XCD at the same time
-// (tiles are numbered x fastest), so that its L2 merges the parts of a line:
-// z-chunk fastest 82.6 us, x fastest 77.4; six z-chunks 96.8 and 85.1.  The
+// (tiles are numbered x fastest, but see launch_adj_t), so that its L2 merges the
+// parts of a line: z-chunk fastest 82.6 us, x fastest 77.4; six z-chunks 96.8 and 85.1.  The
 // carried terms count where arithmetic is added to the same accesses: wind and
 // coefficient gradients in one pass over 512x512x64 226 us before, 208 now.
 #include "pw_bc.h"
@@ -68,6 +68,7 @@ template <typename T> struct AdjK {
     int64_t in_sz, out_sz;
     int32_t in_sy, out_sy;
     int32_t ntx, nty, nzc, zlen, wpb;
+    int32_t zfirst;   // tiles numbered z-chunk fastest (else x fastest), see launch_adj_t
     // coefficient partials (modes with kModeCg): ws[q][level][strip], strip = ty * ntx + tx
     double *ws;
     // boundary rules by addressing (modes with kModeBc), see FwdArgs
@@ -446,10 +447,11 @@ __global__ __launch_bounds__(MaxT) void pw_adjoint_kernel(AdjK<T> a) {
     // wavefront index as a scalar, so that per-strip conditions stay scalar
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int t = xcd_tile(blockIdx.x, gridDim.x);
-    const int tx = t % a.ntx;   // x fastest: neighbours share cache lines of every row they store
-    const int t2 = t / a.ntx;
-    const int cz = t2 % a.nzc;
-    const int ty = (t2 / a.nzc) * a.wpb + wave;
+    const int fast = a.zfirst ? a.nzc : a.ntx, slow = a.zfirst ? a.ntx : a.nzc;
+    const int t2 = t / fast, f = t - t2 * fast, g = t2 % slow;
+    const int tx = a.zfirst ? g : f;   // x fastest: neighbours share cache lines of every row they store
+    const int cz = a.zfirst ? f : g;
+    const int ty = (t2 / slow) * a.wpb + wave;
     if (ty >= a.nty) return;
 
     const int px = a.nx + 2 * a.h, py = a.ny + 2 * a.h, pz = a.nz + 2 * a.h;
@@ -609,6 +611,14 @@ pw_status launch_adj_t(const AdjArgs &g, const TileCfg &cfg, double *ws, hipStre
     a.zlen = cfg.zlen;
     a.nzc = static_cast<int32_t>((pz + cfg.zlen - 1) / cfg.zlen);
     a.wpb = cfg.wpb;
+    // Two strips in x of which the second is at most two thirds full: numbered x
+    // fastest every other tile is a light one, and they gather on the same
+    // compute units.  FP32 with coefficient gradients 79x519x182 116.0 us x
+    // fastest, 100.6 z fastest; 91x221x229 69.9 / 63.4, winds alone FP64
+    // 72x261x167 78.5 / 70.1; 178 such grids 2 % faster in the mean, the worst 3 %
+    // slower.  With a fuller second strip there is nothing in it (89 grids), and
+    // 122x300x100 FP64, two full strips, takes 66.8 / 69.0.
+    a.zfirst = a.ntx == 2 && px - kWaveCols < 40;
     const int64_t nblk_y = (a.nty + cfg.wpb - 1) / cfg.wpb;
     const int64_t nblocks = static_cast<int64_t>(a.ntx) * nblk_y * a.nzc;
     if (nblocks <= 0 || nblocks > 0x7fffffffLL) return fail(PW_ERR_UNSUPPORTED, "grid too large");
