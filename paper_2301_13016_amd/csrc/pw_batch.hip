@@ -149,10 +149,11 @@ hipError_t launch_batch(const TileCfg &c, dim3 g, dim3 b, hipStream_t s, const B
 // Shape of a batch of `points` points: four-row strips of the width that suits
 // each subdomain (four columns: two rows), one plane ahead.  Longer items where
 // the batch is large enough that its tail does not count.  Measured on uneven
-// subdomains, chunks of 32 and of 16 levels and four columns for all (two rows,
-// 64 levels, two planes ahead): 64 subdomains (213 M points) 1.10, 1.13 and
-// 1.32 ms; 32 (88 M) 0.50, 0.51 and 0.64 ms; 8 (40 M) 0.236, 0.230 and 0.245
-// ms; 4 (8 M) 0.064, 0.067 and 0.109 ms.
+// subdomains with buffers of their own, chunks of 32 and of 16 levels and four
+// columns for all (two rows, 64 levels, two planes ahead): 64 subdomains (213 M
+// points) 1.10, 1.13 and 1.32 ms (in pooled buffers 1.23 with chunks of 32); 32
+// (88 M) 0.50, 0.51 and 0.64 ms; 8 (40 M) 0.236, 0.230 and 0.245 ms; 4 (8 M)
+// 0.064, 0.067 and 0.109 ms.
 TileCfg default_batch_tile(int64_t points) { return TileCfg{0, 4, points >= 48000000 ? 32 : 16, 4, 1, 0}; }
 
 }  // namespace

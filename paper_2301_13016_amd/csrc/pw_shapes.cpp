@@ -15,21 +15,21 @@
 // share, but at least 0.8: below that the wavefronts in flight no longer
 // saturate the memory and the round is as long as its latency.  Marches cut
 // into as many chunks as one round holds are tried beside the fixed counts
-// (3 % over 72 grids whose pick it changed).  `cost` is a
-// shape's time per level of a full round, in arbitrary units, and shapes of
-// different widths compete through their wavefront counts: a strip that a
-// narrow grid half fills costs as much as a full one.
+// (3 % over 72 grids whose pick it changed).  `cost` is a shape's time per level
+// of a full round, in arbitrary units within a list, and shapes of different
+// widths compete through their wavefront counts: a strip that a narrow grid half
+// fills costs as much as a full one, and at the grid's x end `ragged` times as
+// much.  Tall shapes read less and take longer to start, so that small grids
+// leave them to the others without a line in the number of points.
 //
-// The constants are fitted to sweeps over every shape on 46 grids for FP32, 17
-// for FP64 and 16-bit storage, 19 for the z-fastest and the tangent kernels
-// (16 x 16 x 16 to 1024 x 1024 x 64, most of them ragged).  The rule's pick
-// is 2 % (FP32), 2 % (FP64), 1 % (16-bit), 4 % (z-fastest, tangent) slower
-// than the best shape of the sweep in the geometric mean.  The fixed shape with
-// "about 2048 wavefronts, chunks of at least 8 levels" that it replaces was
-// 1.5 to 1.65 times slower than the pick: 9.5 -> 3.5 us at 32x32x64 (chunks
-// of one level: a march of eight is latency, and the grid has too few strips
-// to hide it), 130 -> 42 us at 42x587x244 (one column per lane where four
-// leave 5 lanes in 6 idle), 70 -> 43 us at 300x300x75.
+// The constants are fitted to sweeps over shapes and march lengths, whose grids
+// and error stand with each list (2 to 7 % slower than the best shape of the
+// sweep in the geometric mean; 16 x 16 x 16 to 1024 x 1024 x 256, most of them
+// ragged).  The fixed shape with "about 2048 wavefronts, chunks of at least 8
+// levels" that the rule replaced was 1.5 to 1.65 times slower than its picks: 9.5
+// -> 3.5 us at 32x32x64 (chunks of one level: a march of eight is latency, and
+// the grid has too few strips to hide it), 130 -> 42 us at 42x587x244 (one
+// column per lane where four leave 5 lanes in 6 idle), 70 -> 43 us at 300x300x75.
 #include <algorithm>
 
 #include "pw_internal.h"

@@ -260,12 +260,13 @@ __device__ __forceinline__ void bc_strip_codes(StripAddr<RY> &s, uint32_t bcv, i
 // last row of the array's last plane has no memory behind it; there `lim`
 // (every other plane: no limit) pulls the start back, which moves other
 // columns into the last lanes of that row -- the halo edge row above the top
-// plane, which no output reads (with rows of at least PX - 1 elements, which
-// the launch sees to).  These strips once loaded every element by itself from a
-// clamped address, four times the load instructions of a full strip and as
-// many cache requests per byte: 201x143x117 FP32 took 47.4 us, now 29.7 in the
-// same launch shape.  Kernels built for boundary rules (Bc) read one-column lanes
-// at the mapped column and patch wider ones afterwards (bc_patch_x).
+// plane, which no output reads.  Padded rows must have PX - 1 elements for that:
+// any row does for up to four columns per lane, and launch_forward sees to it
+// for eight.  Loading every element by itself from a clamped address took four
+// times the load instructions of a full strip and as many cache requests per
+// byte: 201x143x117 FP32 47.4 us, whole vectors 28.9 in the same launch shape.
+// Kernels built for boundary rules (Bc) read one-column lanes at the mapped
+// column and patch wider ones afterwards (bc_patch_x).
 template <typename Tin, int PX, bool Full, int Bc = 0>
 __device__ __forceinline__ void load_row(typename Vec<Tin, PX>::type &dst, const char *plane, uint32_t off,
                                          uint32_t lim, int col, int last_col, int n, int h, int bc) {
@@ -570,9 +571,10 @@ __device__ __forceinline__ int xcd_tile(int b, int nb) {
 // One work item: the wavefront's strip (tx, ty) marched through z-chunk cz.
 // All 64 lanes must be active (the cross-lane moves read every lane).  Full:
 // the strip lies wholly inside the grid in x ((tx+1)*64*PX <= nx), so every
-// lane loads whole vectors and owns PX outputs; otherwise loads are clamped
-// element-wise (one-column lanes need no clamping beyond their start column)
-// and each lane stores only its columns inside the grid.  Depth: planes in
+// lane owns PX outputs; otherwise the vectors of the last lanes run past the
+// row's end (load_row; under boundary rules the one mapped halo column is
+// patched, bc_patch_x) and each lane stores only its columns inside the grid.
+// Depth: planes in
 // flight ahead of the three a level reads (1 or 2).  Epi: the fused
 // epilogue out = c + alpha * F; the addend rows of level kk are loaded at the
 // start of the level, before that level's plane prefetch (a scheduling
