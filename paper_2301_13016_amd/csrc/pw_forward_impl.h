@@ -85,7 +85,8 @@ __global__ __launch_bounds__(64 * W) void pw_forward_lds_kernel(FwdK<Tin> a) {
     const int tx = t2 % a.ntx;
     const int ty = (t2 / a.ntx) * W + wave;
     if constexpr (Whole)
-        strip_march_lds_f<Tin, PX, RY, Depth, Epi, Bc, W, true, NtOwn>(a, L, tx, ty, cz, wave);
+        strip_march_lds_f<Tin, PX, RY, Depth, Epi, Bc, W, true, NtOwn, sizeof(Tin) == 8 && W == 4>(a, L, tx, ty, cz,
+                                                                                                  wave);
     else
         strip_march_lds<Tin, PX, RY, Depth, Epi, Bc, W, NtOwn>(a, L, tx, ty, cz, wave);
 }
@@ -258,7 +259,7 @@ void launch_lds_b(const FwdK<Tin> &a, const FwdArgs &g, dim3 grid, dim3 block, h
     }
     if constexpr (Bc == 0 && RY == 4) {
         // four-row strips fill the register file, and code that a grid of whole
-        // strips never runs costs it registers: 1024x1024x256 FP64 2.29 -> 2.22
+        // strips never runs costs it registers: 1024x1024x256 FP64 2.29 -> 2.20
         // ms, FP16 0.94 -> 0.91, FP32 1.13 -> 1.09
         if (!g.epilogue && g.nx % (64 * PX) == 0) {
             hipLaunchKernelGGL((pw_forward_lds_kernel<Tin, PX, RY, 1, 0, Bc, W, NtOwn, true>), grid, block, 0, s, a);

@@ -897,7 +897,7 @@ __device__ __forceinline__ void get_edges(const EdgeLds<Tin, PX, W> &L, int slot
 // completed at the two levels before.  Every wavefront of the workgroup runs
 // the same number of levels (same z-chunk), also one whose strip lies past
 // the grid (it loads clamped rows and stores nothing), so the barriers match.
-template <typename Tin, int PX, int RY, bool Full, int Depth, int Epi, int Bc, int W, int Role, bool NtOwn = false>
+template <typename Tin, int PX, int RY, bool Full, int Depth, int Epi, int Bc, int W, int Role, bool NtOwn, bool Fence>
 __device__ __forceinline__ void strip_march_lds_t(const FwdK<Tin> &a, EdgeLds<Tin, PX, W> &L, int tx, int ty,
                                                   int cz, int wave) {
     using Tc = typename Storage<Tin>::Tc;
@@ -966,11 +966,19 @@ __device__ __forceinline__ void strip_march_lds_t(const FwdK<Tin> &a, EdgeLds<Ti
         }                                                                \
         PW_PLOAD(P, kp);                                                 \
     } while (0)
+    // (Fence: the arithmetic of the level stays behind the reads of the
+    // neighbours' rows; left alone, the compiler draws some of it up among
+    // them.  It pays in one instance only, FP64 on grids of whole strips,
+    // where 1024x1024x256 took 2.220 ms without and takes 2.204 with it,
+    // 1024x512x256 1.100 and 1.093.  With two wavefronts 512x512x64 lost
+    // 9 %, with ragged strips addends lost up to a fifth and boundary rules a
+    // tenth.)
 #define PW_SHARE(P)                                                      \
     do {                                                                 \
         put_edges<Tin, PX, RY, W, Role>(L, slot, wave, lane, P);         \
         __syncthreads();                                                 \
         get_edges<Tin, PX, RY, W, Role>(L, slot, wave, lane, P);         \
+        if constexpr (Fence) __builtin_amdgcn_sched_barrier(0);          \
         slot = slot == kLdsSlots - 1 ? 0 : slot + 1;                     \
         if constexpr (Bc && !Full && PX > 1) bc_patch_x<Tin, PX, RY>(P, s); \
         if constexpr (Bc == 2) bc_values<Tin, PX, RY, Full>(P, s, a.bcv); \
@@ -1040,16 +1048,17 @@ __device__ __forceinline__ void strip_march_lds_t(const FwdK<Tin> &a, EdgeLds<Ti
 // Dispatch of one wavefront of an LDS-sharing workgroup to its role's march
 // (the wave index is wave-uniform, so this branch is taken once, before any
 // load), and to the full-strip or x-edge path.
-template <typename Tin, int PX, int RY, int Depth, int Epi, int Bc, int W, bool Full, bool NtOwn>
+template <typename Tin, int PX, int RY, int Depth, int Epi, int Bc, int W, bool Full, bool NtOwn,
+          bool Fence = false>
 __device__ __forceinline__ void strip_march_lds_f(const FwdK<Tin> &a, EdgeLds<Tin, PX, W> &L, int tx, int ty,
                                                   int cz, int wave) {
     static_assert(W >= 2, "sharing needs two wavefronts or more");
     if (wave == 0)
-        strip_march_lds_t<Tin, PX, RY, Full, Depth, Epi, Bc, W, kRoleLo, NtOwn>(a, L, tx, ty, cz, wave);
+        strip_march_lds_t<Tin, PX, RY, Full, Depth, Epi, Bc, W, kRoleLo, NtOwn, Fence>(a, L, tx, ty, cz, wave);
     else if (wave == W - 1)
-        strip_march_lds_t<Tin, PX, RY, Full, Depth, Epi, Bc, W, kRoleHi, NtOwn>(a, L, tx, ty, cz, wave);
+        strip_march_lds_t<Tin, PX, RY, Full, Depth, Epi, Bc, W, kRoleHi, NtOwn, Fence>(a, L, tx, ty, cz, wave);
     else if constexpr (W > 2)
-        strip_march_lds_t<Tin, PX, RY, Full, Depth, Epi, Bc, W, kRoleMid, NtOwn>(a, L, tx, ty, cz, wave);
+        strip_march_lds_t<Tin, PX, RY, Full, Depth, Epi, Bc, W, kRoleMid, NtOwn, Fence>(a, L, tx, ty, cz, wave);
 }
 
 template <typename Tin, int PX, int RY, int Depth, int Epi, int Bc, int W, bool NtOwn = false>
