@@ -168,7 +168,8 @@ typedef struct {
 
 /* pw_advect with an explicit launch shape; tile == NULL means the library's
  * choice (the tuned shape for this grid class if pw_tune has run, else a
- * fixed default).  Same contract and results as pw_advect. */
+ * built-in entry or the cost rule's pick, see pw_tune).  Same contract and
+ * results as pw_advect. */
 pw_status pw_advect_ex(const pw_grid *grid, const pw_layout *layout, pw_dtype in_dtype,
                        const void *u, const void *v, const void *w,
                        const pw_coeffs *coeffs,
@@ -315,18 +316,20 @@ pw_status pw_advect_adjoint_coeff_grad(const pw_grid *grid, const pw_layout *lay
  * [-10, 10), which also serve as cotangents, directions in [-1, 1) and
  * coefficients in [0.0025, 0.0075), since kernel times depend on the data),
  * rotating over as many copies as span about 1 GiB so that repeats are not
- * served by the MALL.  Each candidate is timed over 12 launches; the eight
- * fastest are re-timed in three interleaved rounds of 40 and ranked by their
- * median.  The fastest shape per shape class -- kernel, dtype and the
- * power-of-two ceilings of nx, ny, nz -- goes into a process-wide table that
- * the kernels consult when called without a tile.  The z-cut is kept as a
+ * served by the MALL.  The shape that untuned calls take is a candidate too.
+ * Each is timed over 12 launches, captured into one graph so that the host's
+ * pace does not enter; the eight fastest are re-timed in three interleaved
+ * rounds of 40 and ranked by their median.  The fastest shape per shape class
+ * -- kernel, dtype and the power-of-two ceilings of nx, ny, nz -- goes into a
+ * process-wide table that the kernels consult when called without a tile.  The z-cut is kept as a
  * number of chunks, so an entry serves every nz of its class.  If the
  * environment variable PWADV_TUNE_CACHE names a file, the table is read from
  * it on first use (unreadable or malformed lines are ignored) and the
  * measured entries are rewritten to it after each pw_tune.  Entries measured
  * on MI355X for some power-of-two grids are built in and used for those grids;
- * for every other size without an entry a cost rule picks the shape.  fwd_best / adj_best (may be NULL) receive the chosen forward and
- * adjoint shapes (pw_launch_shape reports any kernel's).  Allocates device
+ * for every other size without an entry a cost rule picks the shape.
+ * fwd_best / adj_best (may be NULL) receive the chosen forward and adjoint
+ * shapes (pw_launch_shape reports any kernel's).  Allocates device
  * memory; synchronises its own stream. */
 #define PW_TUNE_FORWARD 1
 #define PW_TUNE_ADJOINT 2
@@ -336,8 +339,9 @@ pw_status pw_tune(const pw_grid *grid, pw_dtype dtype, int32_t flags, pw_tile *f
 
 /* The launch shape a kernel takes for this grid and dtype when called with
  * tile == NULL: the tuned entry of its shape class if there is one, else the
- * library's default.  No device work.  PW_ERR_UNSUPPORTED for an adjoint or
- * tangent of a 16-bit dtype. */
+ * library's default.  For the forward that is a call without boundary rules:
+ * untuned pw_advect_bc calls pick from shapes of their own.  No device work.
+ * PW_ERR_UNSUPPORTED for an adjoint or tangent of a 16-bit dtype. */
 typedef enum { PW_KERNEL_FORWARD = 0, PW_KERNEL_ADJOINT = 1, PW_KERNEL_TANGENT = 2, PW_KERNEL_ZFAST = 3 } pw_kernel;
 pw_status pw_launch_shape(pw_kernel kind, const pw_grid *grid, pw_dtype dtype, pw_tile *out);
 
@@ -387,10 +391,10 @@ pw_status pw_batch_capture(pw_batch *batch, void *hip_stream);
  * has not been captured since its last re-tiling). */
 pw_status pw_batch_replay(pw_batch *batch, void *hip_stream);
 
-/* Autotuner: times candidate launch shapes on the batch's own buffers
- * (outputs are overwritten with valid results), keeps the fastest, rebuilds
- * the work list for it and drops any captured graph.  Synchronises
- * hip_stream.  If `chosen` is non-NULL it receives the shape. */
+/* Autotuner: times candidate launch shapes, the batch's present one among
+ * them, on the batch's own buffers (outputs are overwritten with valid
+ * results), keeps the fastest, rebuilds the work list for it and drops any
+ * captured graph.  Synchronises hip_stream.  If `chosen` is non-NULL it receives the shape. */
 pw_status pw_batch_tune(pw_batch *batch, void *hip_stream, pw_tile *chosen);
 
 /* Current launch shape and work-list size of a batch. */
